@@ -24,6 +24,10 @@
 //   (coalesced), and bias / gate are one value per lane.  Workgroups are
 //   remapped so each XCD (8 per MI355X, own L2) works on a contiguous group
 //   of tiles that share activation rows.
+//   Launches whose 256 x 256 tiles would leave CUs idle (few rows) take
+//   256 x 128, 128 x 128 or 64 x 64 tiles (gemm_ring_kernel): one 1560-token
+//   30-block step 8.62 -> 6.73 ms, the 1024-token loop 5.47 -> 3.26 ms, a
+//   226 x 3072 x 3072 product 52.5 -> 11.8 us.
 // fp32 path: a plain 64 x 64 register-blocked VALU kernel for the fp32
 //   configuration (small shapes, latency-bound).
 #include <atomic>
@@ -193,18 +197,18 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t T) {
   return (x < r) ? x * (q + 1) + local : r * (q + 1) + (x - r) * q + local;
 }
 
-// Tile t -> (tm, tn) in groups of kGroupM token tiles, feature tiles inner.
+// Tile t -> (tm, tn) in groups of GM token tiles, feature tiles inner.
 // The 32 tiles an XCD runs at once then share few activation row blocks
 // (streamed once from HBM) and many weight column blocks (re-read by every
 // row block, so they come from the on-package cache): groups of 2 measured
 // 3-6% faster than 8 on the model shapes here (4 and 3 within noise of 2).
-constexpr int kGroupM = 2;
+template <int GM = 2>
 __device__ __forceinline__ void tile_coords(int64_t t, int64_t tiles_m, int tiles_n, int64_t& tm,
                                             int& tn) {
-  const int64_t per_group = (int64_t)kGroupM * tiles_n;
+  const int64_t per_group = (int64_t)GM * tiles_n;
   const int64_t g = t / per_group;
-  const int64_t first = g * kGroupM;
-  const int64_t gsize = min((int64_t)kGroupM, tiles_m - first);
+  const int64_t first = g * GM;
+  const int64_t gsize = min((int64_t)GM, tiles_m - first);
   const int64_t w = t - g * per_group;
   tm = first + w % gsize;
   tn = (int)(w / gsize);
@@ -243,43 +247,41 @@ __device__ __forceinline__ uint64_t uniform_ptr(const void* p) {
 }
 __device__ __forceinline__ void wait_all() { __builtin_amdgcn_s_waitcnt(0); }
 
-// Epilogue of one 256 x 256 tile: wave (wm, wn) stores its 128 x 64 block
-// from the MFMA accumulators.
-template <int KIND>
-__device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[4][2], int64_t M,
-                                              int N, int64_t m0, int n0, int wm, int wn,
-                                              int lane) {
+// Epilogue of one wave's block of an output tile: 32 MB rows from mw and
+// 32 NB columns from nw, out of the MFMA accumulators.  full: every row of
+// the block is below M.
+template <int KIND, int MB, int NB, int LOADS = 32>
+__device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[MB][NB], int64_t M,
+                                              int N, int64_t mw, int nw, bool full, int lane) {
   const int lr = lane & 31, lg = lane >> 5;
   // D[i][j] of a 32x32 block: j = lane % 32, i = 8 (r / 4) + 4 (lane / 32) + r % 4.
   // A lane owns one feature column per 32-wide block: set up its epilogue
-  // once, then handle its 64 rows of that column.  Full tiles skip the row
+  // once, then handle its 16 MB rows of that column.  Full tiles skip the row
   // check (a per-element branch would serialise every load behind a wait);
-  // read-modify-write kinds issue 32 loads before their stores.
-  const bool full = m0 + BM <= M;
-  const int64_t mrow = m0 + wm * 128 + 4 * lg;
+  // read-modify-write kinds issue up to LOADS loads before their stores.
+  const int64_t mrow = mw + 4 * lg;
   if constexpr (KIND == ACID_EPI_QKV || KIND == ACID_EPI_QKV_GELU) {
     // V columns are rows of V^T, whose tokens are contiguous: a lane holds 4
     // consecutive tokens per group r / 4 and its partner lane (l ^ 32) the
     // next 4, so one permlane32 swap per dword gives each lane 8 consecutive
     // tokens: 16-byte stores instead of 2-byte ones scattered over 32 rows.
-    const int nw = n0 + wn * 64;
-    if (full && nw >= 2 * e.H && nw + 64 <= 3 * e.H) {  // all 64 columns in V
+    if (full && nw >= 2 * e.H && nw + 32 * NB <= 3 * e.H) {  // all columns in V
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
+      for (int nb = 0; nb < NB; ++nb) {
         const int n = nw + nb * 32 + lr;
         const int cc = n - 2 * e.H;
         const int head = cc / e.head_dim, dd = cc - head * e.head_dim;
         bf16* vrow = static_cast<bf16*>(e.vt) + ((int64_t)head * e.head_dim + dd) * e.vt_ld;
         const float bias = e.bias[n];
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
+        for (int mb = 0; mb < MB; ++mb) {
           uint32_t w[8];  // tokens 8 (r / 4) + 4 lg + r % 4 as bf16 pairs
 #pragma unroll
           for (int r = 0; r < 16; r += 2) {
             const bf16x2 pr = {(bf16)(acc[mb][nb][r] + bias), (bf16)(acc[mb][nb][r + 1] + bias)};
             w[r / 2] = __builtin_bit_cast(uint32_t, pr);
           }
-          const int64_t t0 = m0 + wm * 128 + mb * 32 + 8 * lg;
+          const int64_t t0 = mw + mb * 32 + 8 * lg;
 #pragma unroll
           for (int p = 0; p < 2; ++p) {  // groups 2p (tokens +0..7) and 2p + 1 (+8..15)
             uint32_t lo[2], hi[2];
@@ -298,33 +300,43 @@ __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[4][2],
       return;
     }
   }
+  const int rows_left = (int)(M - mrow < 32 * MB ? M - mrow : 32 * MB);
   if constexpr (!ColEpi<KIND, bf16>::kRmw) {
     if (full) {
-      // The two 32-column blocks of a wave fill the two halves of the same
+      // The 32-column blocks of a wave fill the two halves of the same
       // 128-byte line of each output row (bf16): store them back to back so
       // the line is complete in the L2 before it can be written back.
-      const ColEpi<KIND, bf16> c0(e, n0 + wn * 64 + lr, N), c1(e, n0 + wn * 64 + 32 + lr, N);
+      if constexpr (NB == 2) {
+        const ColEpi<KIND, bf16> c0(e, nw + lr, N), c1(e, nw + 32 + lr, N);
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t m = mrow + mb * 32 + 8 * (r >> 2) + (r & 3);
-          c0.put(m, acc[mb][0][r]);
-          c1.put(m, acc[mb][1][r]);
-        }
+          for (int r = 0; r < 16; ++r) {
+            const int64_t m = mrow + mb * 32 + 8 * (r >> 2) + (r & 3);
+            c0.put(m, acc[mb][0][r]);
+            c1.put(m, acc[mb][1][r]);
+          }
+      } else {
+        static_assert(NB == 1, "one or two column blocks per wave");
+        const ColEpi<KIND, bf16> c0(e, nw + lr, N);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            c0.put(mrow + mb * 32 + 8 * (r >> 2) + (r & 3), acc[mb][0][r]);
+      }
       return;
     }
     // The ragged last row tile: row offsets from mrow in 32 bits (a 64-bit
     // row per element made the register allocator spill).
-    const int rows_left = (int)(M - mrow < 128 ? M - mrow : 128);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const ColEpi<KIND, bf16> ce(e, n0 + wn * 64 + nb * 32 + lr, N);
+    for (int nb = 0; nb < NB; ++nb) {
+      const ColEpi<KIND, bf16> ce(e, nw + nb * 32 + lr, N);
       // The column's bias has landed before the guarded stores: a load still
       // in flight there makes every guarded block wait for all earlier stores.
       asm volatile("" ::"v"(ce.bias));
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int dr = mb * 32 + 8 * (r >> 2) + (r & 3);
@@ -332,61 +344,53 @@ __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[4][2],
         }
     }
     return;
-  }
+  } else {
+    constexpr int G = MB % 2 || LOADS < 32 ? 1 : 2;  // row blocks per batch of loads
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
-    const int n = n0 + wn * 64 + nb * 32 + lr;
-    ColEpi<KIND, bf16> ce(e, n, N);
-    if (full) {
-      if constexpr (ColEpi<KIND, bf16>::kRmw) {
+    for (int nb = 0; nb < NB; ++nb) {
+      const ColEpi<KIND, bf16> ce(e, nw + nb * 32 + lr, N);
+      if (full) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {  // 32 loads in flight, then 32 stores
-          float prev[2][16];
+        for (int h = 0; h < MB / G; ++h) {  // a batch of loads in flight, then the stores
+          float prev[G][16];
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              prev[mb][r] = ce.old(mrow + (2 * h + mb) * 32 + 8 * (r >> 2) + (r & 3));
-#pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
+          for (int mb = 0; mb < G; ++mb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              ce.put_old(mrow + (2 * h + mb) * 32 + 8 * (r >> 2) + (r & 3),
-                         acc[2 * h + mb][nb][r], prev[mb][r]);
+              prev[mb][r] = ce.old(mrow + (G * h + mb) * 32 + 8 * (r >> 2) + (r & 3));
+#pragma unroll
+          for (int mb = 0; mb < G; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              ce.put_old(mrow + (G * h + mb) * 32 + 8 * (r >> 2) + (r & 3),
+                         acc[G * h + mb][nb][r], prev[mb][r]);
         }
       } else {
+        // The ragged last row tile of a read-modify-write kind: loads from rows
+        // clamped to M - 1 (always valid) batched as above, stores guarded.  A
+        // load under the store's guard would wait for each element in turn.
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int h = 0; h < MB / G; ++h) {
+          float prev[G][16];
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            ce.put(mrow + mb * 32 + 8 * (r >> 2) + (r & 3), acc[mb][nb][r]);
-      }
-    } else {
-      // The ragged last row tile of a read-modify-write kind: loads from rows
-      // clamped to M - 1 (always valid) batched as above, stores guarded.  A
-      // load under the store's guard would wait for each element in turn.
-      const int rows_left = (int)(M - mrow < 128 ? M - mrow : 128);
+          for (int mb = 0; mb < G; ++mb)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        float prev[2][16];
+            for (int r = 0; r < 16; ++r) {
+              const int dr = (G * h + mb) * 32 + 8 * (r >> 2) + (r & 3);
+              prev[mb][r] = ce.old(dr < rows_left ? mrow + dr : M - 1);
+            }
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+          for (int mb = 0; mb < G; ++mb)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int dr = (2 * h + mb) * 32 + 8 * (r >> 2) + (r & 3);
-            prev[mb][r] = ce.old(dr < rows_left ? mrow + dr : M - 1);
-          }
+            for (int r = 0; r < 16; ++r) asm volatile("" ::"v"(prev[mb][r]));  // loads land here
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+          for (int mb = 0; mb < G; ++mb)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) asm volatile("" ::"v"(prev[mb][r]));  // loads land here
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int dr = (2 * h + mb) * 32 + 8 * (r >> 2) + (r & 3);
-            if (dr < rows_left) ce.put_old(mrow + dr, acc[2 * h + mb][nb][r], prev[mb][r]);
-          }
+            for (int r = 0; r < 16; ++r) {
+              const int dr = (G * h + mb) * 32 + 8 * (r >> 2) + (r & 3);
+              if (dr < rows_left) ce.put_old(mrow + dr, acc[G * h + mb][nb][r], prev[mb][r]);
+            }
+        }
       }
     }
   }
@@ -626,7 +630,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_bf16_kernel(const bf16* A
         }
     return;
   }
-  tile_epilogue<KIND>(e, acc, M, N, m0, n0, wm, wn, lane);
+  tile_epilogue<KIND, 4, 2>(e, acc, M, N, m0 + wm * 128, n0 + wn * 64, m0 + BM <= M, lane);
 }
 
 // The split tiles: partial sums added in split order (deterministic), then
@@ -663,7 +667,152 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_split_reduce_kernel(int64
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[mb][nb][4 * r4 + i] = v[i];
       }
-  tile_epilogue<KIND>(e, acc, M, N, m0, n0, wm, wn, lane);
+  tile_epilogue<KIND, 4, 2>(e, acc, M, N, m0 + wm * 128, n0 + wn * 64, m0 + BM <= M, lane);
+}
+
+// ------------------------------------------------- bf16 MFMA, few tiles
+
+// The same product for grids that the 256 x 256 tiles leave mostly idle
+// (short sequences, few rows): TM x TN tiles, WM x WN waves that only read
+// fragments and issue MFMAs, and four waves that only issue the operand
+// DMAs, one on each SIMD beside them.  A K-step of 64 of both operands is
+// one stage of a ring of NST stages, each refilled NST - 1 stages ahead; one
+// barrier per stage, before the last sub-step of 16, so the next stage's
+// first fragment reads run under its MFMAs.  A tile accumulates its K-steps
+// in the order of the 256 x 256 kernel with the same instruction, so results
+// do not depend on the tile size, bit for bit.
+// A 128 x 128 stage takes about 0.41 us of a CU with 156 tiles in flight
+// (0.36 without the DMAs, 0.31 for one tile per XCD alone; its MFMAs need
+// 0.22 us at 2.4 GHz): the MFMA waves' issue between barriers bounds it, not
+// the staging.  Reading fragments three sub-steps ahead instead of one, or a
+// ring one stage deeper, changes nothing (57-60 us at 1560 x 1536 x 8960);
+// eight MFMA waves instead of four 2-10% faster.
+template <int KIND, int TM, int TN, int WM, int WN, int NST, int OCC>
+__global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
+    const bf16* A, const bf16* Wt, int64_t M, int N, int K, Epi e) {
+  if (e.pred && *e.pred == 0) return;
+  constexpr int kMath = WM * WN;                       // MFMA waves
+  constexpr int MB = TM / WM / 32, NB = TN / WN / 32;  // 32 x 32 blocks per wave
+  constexpr int kStageElems = (TM + TN) * BK;
+  constexpr int ND = (TM + TN) / 8 / 4;                // 1 KB DMAs per DMA wave and stage
+  static_assert((TM + TN) % 32 == 0 && NST >= 2 && ND * (NST - 1) <= 63, "ring");
+  __shared__ __attribute__((aligned(1024))) bf16 ring[NST * kStageElems];
+
+  const int tiles_n = N / TN;
+  const int64_t tiles_m = (M + TM - 1) / TM;
+  int64_t tm;
+  int tn;
+  tile_coords<4>(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
+  const int64_t m0 = tm * TM;
+  const int n0 = tn * TN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int NS = K / BK;
+
+  if (wave >= kMath) {
+    // DMA i of DMA wave w fills 1 KB block b = w ND + i of a stage: 8 rows of
+    // the A tile (the first TM / 8 blocks) or of the B tile, 128 bytes each,
+    // chunks at the slots of the 256 x 256 kernel's tiles.  Rows past M are
+    // clamped.
+    uint64_t base[ND];
+    uint32_t off[ND];
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int b = (wave - kMath) * ND + i;
+      const bool is_a = b < TM / 8;
+      const int r = (is_a ? b : b - TM / 8) * 8 + (lane >> 3);
+      const int ch = (lane & 7) ^ ((r >> 1) & 7);
+      const int row = is_a && m0 + r >= M ? (int)(M - 1 - m0) : r;
+      base[i] = uniform_ptr(is_a ? A + m0 * K : Wt + (int64_t)n0 * K);
+      off[i] = (uint32_t)(row * K + ch * 8) * 2u;
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)ring) +
+                          (uint32_t)((wave - kMath) * ND) * 1024u;
+    auto issue = [&](int st, uint32_t buf) {
+      const uint32_t kb = (uint32_t)st * (BK * 2);
+#pragma unroll
+      for (int i = 0; i < ND; ++i)
+        dma16(base[i] + kb, off[i], lds0 + buf * (uint32_t)(kStageElems * 2) + i * 1024u);
+    };
+    // vmcnt(n), no other counter
+#define RING_WAIT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+      if (st < NS) issue(st, st);
+    if (NS >= NST)
+      RING_WAIT(ND * (NST - 1));  // stage 0 landed
+    else
+      RING_WAIT(0);
+    __builtin_amdgcn_s_barrier();
+    uint32_t buf = 0;
+    for (int st = 0; st < NS; ++st) {
+      // stage st + 1 landed: NST - 2 younger stages may be in flight
+      if (st + NST - 1 < NS)
+        RING_WAIT(ND * (NST - 2));
+      else
+        RING_WAIT(0);
+      __builtin_amdgcn_s_barrier();  // stage st read by all: its buffer is free
+      if (st + NST < NS) issue(st + NST, buf);
+      buf = buf + 1 == NST ? 0 : buf + 1;
+    }
+#undef RING_WAIT
+    return;
+  }
+
+  const int wm = wave / WN, wn = wave % WN;
+  const int lr = lane & 31, lg = lane >> 5;
+  const int a_rbase = (wm * (TM / WM) + lr) * BK;
+  const int b_rbase = (TM + wn * (TN / WN) + lr) * BK;
+  int sl[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) sl[kk] = 8 * ((2 * kk + lg) ^ ((lr >> 1) & 7));
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  bf16x8 fa[2][MB], fb[2][NB];
+  auto read_frags = [&](const bf16* stage, int kk) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+      fa[kk & 1][mb] = *reinterpret_cast<const bf16x8*>(stage + a_rbase + mb * 32 * BK + sl[kk]);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      fb[kk & 1][nb] = *reinterpret_cast<const bf16x8*>(stage + b_rbase + nb * 32 * BK + sl[kk]);
+  };
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read_frags(ring, 0);
+  int buf = 0;
+  for (int st = 0; st < NS; ++st) {
+    const bf16* cur = ring + buf * kStageElems;
+    buf = buf + 1 == NST ? 0 : buf + 1;
+    const bf16* nxt = ring + buf * kStageElems;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      if (kk < 3) {
+        read_frags(cur, kk + 1);
+      } else {
+        // the stage's last fragments have arrived: its buffer may be refilled
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read_frags(nxt, 0);  // after the last stage: read and dropped
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk & 1][mb], fb[kk & 1][nb],
+                                                                acc[mb][nb], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  tile_epilogue<KIND, MB, NB, OCC >= 3 ? 16 : 32>(e, acc, M, N, m0 + wm * (TM / WM),
+                                                 n0 + wn * (TN / WN), m0 + TM <= M, lane);
 }
 
 // ------------------------------------------------------------ fp32 VALU
@@ -747,6 +896,49 @@ int choose_split(int64_t tiles, int K, int64_t& rem) {
   return S;
 }
 
+// Output tile of a bf16 launch.  A launch takes ceil(tiles / CUs) rounds of
+// tiles, so its time goes as rounds x tile area x the kernel's time per unit
+// of area, here relative to the 256 x 256 kernel and fitted to timings at K
+// 1024-8960 (microseconds, 256 x 256 / 256 x 128 / 128 x 128 / 64 x 64; the
+// best is what the rule takes):
+//   1024 x 1024, K 4096:   67.8 / 38.3 / 24.7 / 15.5   (16, 32, 64, 256 tiles)
+//   1560 x 1536, K 8960:  138.6 / 84.4 / 57.2 / 78.6   (42, 84, 156, 600)
+//   1560 x 4608, K 1536:   34.8 / 27.3 / 32.7 / 41.3   (126, 252, 468, 1800)
+//   4680 x 1536, K 1536:   36.3 / 29.3 / 33.6 / 39.6   (114, 228, 444, 1776)
+//   9000 x 3072, K 3072:  156.7 / 171.5 / 191.4 / 257.7 (432, 864, 1704, 6768)
+// Smaller tiles move more operand bytes per flop, which is what their larger
+// time per area is; every tile gives the same bits.
+enum class Tile { k256, k256x128, k128, k64 };
+Tile choose_tile(int64_t M, int N, int64_t tiles, int64_t rem, int split) {
+  const int64_t cus = cu_count();
+  auto rounds = [&](int tm, int tn) {
+    return (double)(((M + tm - 1) / tm * (N / tn) + cus - 1) / cus);
+  };
+  // a K split replaces the last round by 1 / split of one and a reduction
+  double best = split > 1 ? (double)((tiles - rem) / cus) * 4 + 4.0 / split + 0.5
+                          : (double)((tiles + cus - 1) / cus) * 4;
+  Tile t = Tile::k256;
+  auto consider = [&](Tile c, double cost) {
+    if (cost < best) {
+      best = cost;
+      t = c;
+    }
+  };
+  consider(Tile::k256x128, rounds(256, 128) * 2 * 1.15);
+  consider(Tile::k128, rounds(128, 128) * 1.3);
+  consider(Tile::k64, rounds(64, 64) * 0.25 * 2.0);
+  return t;
+}
+
+template <int KIND, int TM, int TN, int WM, int WN, int NST, int OCC>
+hipError_t launch_ring(int64_t M, int N, int K, const void* a, const void* wt, const Epi& e,
+                       hipStream_t s) {
+  const int64_t grid = (M + TM - 1) / TM * (N / TN);
+  hipLaunchKernelGGL((gemm_ring_kernel<KIND, TM, TN, WM, WN, NST, OCC>), dim3((unsigned)grid),
+                     dim3(64 * (WM * WN + 4)), 0, s, (const bf16*)a, (const bf16*)wt, M, N, K, e);
+  return hipGetLastError();
+}
+
 template <int KIND>
 hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const void* wt,
                        const Epi& e, hipStream_t s) {
@@ -754,6 +946,12 @@ hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const 
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
     int64_t rem = 0;
     const int split = e.split_ws ? choose_split(tiles, K, rem) : 1;
+    switch (choose_tile(M, N, tiles, rem, split)) {
+      case Tile::k256x128: return launch_ring<KIND, 256, 128, 4, 2, 3, 3>(M, N, K, a, wt, e, s);
+      case Tile::k128: return launch_ring<KIND, 128, 128, 2, 4, 4, 3>(M, N, K, a, wt, e, s);
+      case Tile::k64: return launch_ring<KIND, 64, 64, 2, 2, 4, 4>(M, N, K, a, wt, e, s);
+      case Tile::k256: break;
+    }
     const int64_t tiles_main = tiles - (split > 1 ? rem : 0);
     const int64_t grid = tiles_main + (split > 1 ? rem * split : 0);
     hipLaunchKernelGGL(gemm_bf16_kernel<KIND>, dim3((unsigned)grid), dim3(64 * kWaves), 0, s,
