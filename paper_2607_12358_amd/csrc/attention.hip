@@ -24,8 +24,8 @@
 //   epilogue writes it) the score MFMAs start from -m and deliver the exp2
 //   arguments themselves.  The row sum adds the bf16-rounded probabilities
 //   that the P V product uses.
-// fp32 path: one wave per (head, query), online softmax in fp32 (for the
-//   fp32 configuration).
+// fp32 path: the fp32 matrix instruction, 32 queries per workgroup, the keys
+//   split over its four waves (for the fp32 configuration).
 #include <atomic>
 
 #include "common.h"
@@ -592,73 +592,159 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
 
 // ------------------------------------------------------------------ fp32
 
-// fp32 path (the small fp32 configuration): one wave per (head, query).
-// Lanes take one key each of a 64-key chunk for the scores; the wave max and
-// sum give the online softmax; lane l accumulates output dims l, l + 64, ...
-// over the chunk's probabilities, broadcast one key at a time.
+// fp32 path: flash-style on the fp32 matrix instruction
+// (v_mfma_f32_32x32x2_f32: products and sums in fp32), 32 queries per
+// workgroup.  The four waves hold the same queries and take every fourth
+// tile of 32 keys each, so that the short sequences of the fp32
+// configuration still give two waves per SIMD; their partial softmaxes meet
+// in LDS and are added in wave order.  Scores are formed transposed as in the
+// bf16 path: a lane owns one query and 16 of the tile's keys, and with
+// contraction slot r of half-wave h standing for key 8 (r / 4) + 4 h + r % 4
+// the probabilities in accumulator layout are the B operand of
+// O^T = V^T P^T, and the matching V^T operand is one 16-byte load per four
+// MFMAs.  K and V^T come straight from global memory (16 bytes per lane and
+// four MFMAs of 64 cycles), V of a tile ahead of its score MFMAs, K of the
+// next tile ahead of the softmax; Q is read from LDS.  Bound by the matrix
+// unit (4 L^2 d flops a head at 157 TFLOP/s).  The one-query-per-wave kernel
+// before it took 2239 us at 16 heads x 1013 x 64 (V^T read four bytes a lane
+// from 64 rows), and a 1013-token fp32 block of that width 2824 us; the block
+// takes 609 us with this kernel.
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q,
-                                                       const float* __restrict__ Kp,
-                                                       const float* __restrict__ Vt, int64_t L,
-                                                       int64_t vt_ld, int n_heads,
-                                                       float* __restrict__ O, int64_t o_ld,
-                                                       float scale, const int32_t* pred) {
+__global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restrict__ Q,
+                                                          const float* __restrict__ Kp,
+                                                          const float* __restrict__ Vt, int64_t L,
+                                                          int64_t vt_ld, int n_heads,
+                                                          float* __restrict__ O, int64_t o_ld,
+                                                          float scale, const int32_t* pred) {
   if (pred && *pred == 0) return;
-  constexpr int C = D / 64;  // output dims per lane
-  const int lane = threadIdx.x & 63;
-  const int64_t wq = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wq >= L * n_heads) return;  // whole wave; no barriers below
-  const int head = (int)(wq / L);
-  const int64_t qrow = wq - (int64_t)head * L;
+  constexpr int BT = 32;       // queries per workgroup, keys per tile
+  constexpr int NC = D / 4;    // 16-byte chunks per row
+  constexpr int ND = D / 32;   // 32-row blocks of O^T
+  // Q as [chunk][query] during the loop, the waves' O^T as
+  // [wave][chunk][query] after it.
+  __shared__ f32x4 lds[4 * NC * BT];
+  __shared__ float ml[2][4][BT];
+  const int64_t n_qt = (L + BT - 1) / BT;
+  const int64_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
+  const int head = (int)(item / n_qt);
+  const int64_t q0 = (item - (int64_t)head * n_qt) * BT;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lg = lane >> 5;
   const float* Kh = Kp + (int64_t)head * L * D;
   const float* Vh = Vt + (int64_t)head * D * vt_ld;
-  float q[D];
-  {
-    const float4* q4 = reinterpret_cast<const float4*>(Q + ((int64_t)head * L + qrow) * D);
-#pragma unroll
-    for (int d4 = 0; d4 < D / 4; ++d4) {
-      const float4 v = q4[d4];
-      q[4 * d4] = v.x;
-      q[4 * d4 + 1] = v.y;
-      q[4 * d4 + 2] = v.z;
-      q[4 * d4 + 3] = v.w;
-    }
+  for (int i = tid; i < NC * BT; i += 256) {
+    const int c = i % NC, r = i / NC;
+    const int64_t row = q0 + r < L ? q0 + r : L - 1;
+    lds[c * BT + r] = *reinterpret_cast<const f32x4*>(Q + ((int64_t)head * L + row) * D + 4 * c);
   }
-  float o[C];
+  __syncthreads();
+
+  f32x16 o[ND];
 #pragma unroll
-  for (int c = 0; c < C; ++c) o[c] = 0.f;
+  for (int db = 0; db < ND; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
   float m_run = -__builtin_inff(), l_run = 0.f;
-  for (int64_t j0 = 0; j0 < L; j0 += 64) {
-    const int64_t j = j0 + lane;
-    float s = -__builtin_inff();
-    if (j < L) {
-      const float4* k4 = reinterpret_cast<const float4*>(Kh + j * D);
-      float a = 0.f;
+  const int64_t nt = (L + BT - 1) / BT;
+  f32x4 kf[NC / 2];
+  auto load_k = [&](int64_t t) {
+    const int64_t key = t * BT + lr;
+    const float* kr = Kh + (key < L ? key : L - 1) * D + 4 * lg;
 #pragma unroll
-      for (int d4 = 0; d4 < D / 4; ++d4) {
-        const float4 kv = k4[d4];
-        a += q[4 * d4] * kv.x + q[4 * d4 + 1] * kv.y + q[4 * d4 + 2] * kv.z + q[4 * d4 + 3] * kv.w;
+    for (int j = 0; j < NC / 2; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kr + 8 * j);
+  };
+  if (wave < nt) load_k(wave);
+  for (int64_t t = wave; t < nt; t += 4) {
+    f32x4 vf[ND][4];
+#pragma unroll
+    for (int db = 0; db < ND; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int64_t key0 = t * BT + 8 * g + 4 * lg;
+        vf[db][g] = *reinterpret_cast<const f32x4*>(Vh + (int64_t)(db * 32 + lr) * vt_ld +
+                                                 (key0 < L ? key0 : 0));
       }
-      s = a * scale;
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int j = 0; j < NC / 2; ++j) {
+      const f32x4 qf = lds[(2 * j + lg) * BT + lr];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][i], qf[i], s, 0, 0, 0);
     }
-    const float m_new = fmaxf(m_run, wave_max(s));  // finite: the chunk has a key
-    const float alpha = exp2f(m_run - m_new);
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 4 < nt) load_k(t + 4);
+    __builtin_amdgcn_sched_barrier(0);
+    if (t * BT + BT > L) {  // the ragged last tile: keys past L, V^T's padding
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (t * BT + 8 * g + 4 * lg + e >= L) {
+            s[4 * g + e] = -__builtin_inff();
+#pragma unroll
+            for (int db = 0; db < ND; ++db) vf[db][g][e] = 0.f;
+          }
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    const float m_new = fmaxf(m_run, half_swap_max(mx) * scale);
+    // A tile of -inf scores alone leaves no reference: its probabilities are 0.
+    const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;
+    if (__any(m_new > m_run)) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < ND; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    }
     m_run = m_new;
-    const float p = j < L ? exp2f(s - m_new) : 0.f;
-    l_run = l_run * alpha + wave_sum(p);
 #pragma unroll
-    for (int c = 0; c < C; ++c) o[c] *= alpha;
-    const int cnt = (int)(L - j0 < 64 ? L - j0 : 64);
-    for (int jj = 0; jj < cnt; ++jj) {
-      const float pj = __shfl(p, jj, 64);
-#pragma unroll
-      for (int c = 0; c < C; ++c) o[c] += pj * Vh[(int64_t)(lane + 64 * c) * vt_ld + j0 + jj];
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale, -m_use));
+      l_run += s[r];
     }
-  }
-  const float inv = 1.0f / l_run;
-  float* orow = O + qrow * o_ld + (int64_t)head * D;
 #pragma unroll
-  for (int c = 0; c < C; ++c) orow[lane + 64 * c] = o[c] * inv;
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int db = 0; db < ND; ++db)
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db][r >> 2][r & 3], s[r], o[db], 0, 0, 0);
+  }
+  l_run += __shfl_xor(l_run, 32, 64);
+  __syncthreads();  // every wave is done with Q
+#pragma unroll
+  for (int db = 0; db < ND; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      lds[(wave * NC + (db * 4 + g) * 2 + lg) * BT + lr] =
+          f32x4{o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
+  if (lg == 0) {
+    ml[0][wave][lr] = m_run;
+    ml[1][wave][lr] = l_run;
+  }
+  __syncthreads();
+  for (int i = tid; i < NC * BT; i += 256) {
+    const int r = i % BT, c = i / BT;
+    if (q0 + r >= L) continue;
+    float m = ml[0][0][r];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) m = fmaxf(m, ml[0][w][r]);
+    float l = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {  // a wave without keys has m = -inf, weight 0
+      const float a = __builtin_amdgcn_exp2f(ml[0][w][r] - m);
+      l += a * ml[1][w][r];
+      acc += a * lds[(w * NC + c) * BT + r];
+    }
+    *reinterpret_cast<f32x4*>(O + (q0 + r) * o_ld + (int64_t)head * D + 4 * c) = acc * (1.0f / l);
+  }
 }
 
 // Waves per workgroup: 8 for d = 128 (a staged K/V tile feeds 256 queries),
@@ -693,7 +779,7 @@ template <int D>
 hipError_t launch_f32(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
                       int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s, const int32_t* pred,
                       bool q_prescaled) {
-  dim3 grid((unsigned)((L * n_heads + 3) / 4));
+  dim3 grid((unsigned)((L + 31) / 32 * n_heads));
   hipLaunchKernelGGL(attn_f32_kernel<D>, grid, dim3(256), 0, s, (const float*)q,
                      (const float*)k, (const float*)vt, L, vt_ld, n_heads, (float*)o, o_ld,
                      q_prescaled ? 1.0f : attn_q_scale(D), pred);
