@@ -28,8 +28,8 @@
 //   256 x 128, 128 x 128 or 64 x 64 tiles (gemm_ring_kernel): one 1560-token
 //   30-block step 8.62 -> 6.73 ms, the 1024-token loop 5.47 -> 3.26 ms, a
 //   226 x 3072 x 3072 product 52.5 -> 11.8 us.
-// fp32 path: a plain 64 x 64 register-blocked VALU kernel for the fp32
-//   configuration (small shapes, latency-bound).
+// fp32 path: the fp32 matrix instruction on 64 x 64 or 32 x 32 tiles, for the
+//   fp32 configuration.
 #include <atomic>
 #include <type_traits>
 
@@ -70,34 +70,6 @@ __device__ __forceinline__ T* qkv_dst(const Epi& e, int c, int64_t& stride) {
   }
   stride = 1;
   return static_cast<T*>(e.vt) + ((int64_t)head * e.head_dim + dd) * e.vt_ld;
-}
-
-template <int KIND, typename T>
-__device__ __forceinline__ void epi_elem(const Epi& e, int64_t m, int n, int N, float acc) {
-  float bias = e.bias[n];
-  if (KIND == ACID_EPI_GATE_RESIDUAL && e.bias2) bias += e.bias2[n];
-  const float y = acc + bias;
-  const int64_t idx = m * N + n;
-  if constexpr (KIND == ACID_EPI_BIAS) {
-    static_cast<float*>(e.out)[idx] = y;
-  } else if constexpr (KIND == ACID_EPI_BIAS_GELU) {
-    static_cast<T*>(e.out)[idx] = (T)gelu_tanh(y);
-  } else if constexpr (KIND == ACID_EPI_GATE_RESIDUAL) {
-    float* h = static_cast<float*>(e.out) + idx;
-    *h = *h + e.gate[n] * y;
-  } else if constexpr (KIND == ACID_EPI_QKV || KIND == ACID_EPI_QKV_GELU) {
-    if (KIND == ACID_EPI_QKV || n < e.n_qkv) {
-      int64_t stride;
-      T* dst = qkv_dst<T>(e, n, stride);
-      dst[m * stride] = (T)(n < e.H ? y * e.q_mul : y);
-    } else {
-      static_cast<T*>(e.out)[m * e.out_ld + (n - e.n_qkv)] = (T)gelu_tanh(y);
-    }
-  } else {  // ACID_EPI_EULER
-    if (e.v_out) e.v_out[idx] = y;
-    float* x = static_cast<float*>(e.out) + idx;
-    *x = *x + e.dsigma * y;
-  }
 }
 
 // Epilogue of one output column n: bias, gate and destination are resolved
@@ -250,7 +222,7 @@ __device__ __forceinline__ void wait_all() { __builtin_amdgcn_s_waitcnt(0); }
 // Epilogue of one wave's block of an output tile: 32 MB rows from mw and
 // 32 NB columns from nw, out of the MFMA accumulators.  full: every row of
 // the block is below M.
-template <int KIND, int MB, int NB, int LOADS = 32>
+template <int KIND, typename T, int MB, int NB, int LOADS = 32>
 __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[MB][NB], int64_t M,
                                               int N, int64_t mw, int nw, bool full, int lane) {
   const int lr = lane & 31, lg = lane >> 5;
@@ -271,29 +243,39 @@ __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[MB][NB
         const int n = nw + nb * 32 + lr;
         const int cc = n - 2 * e.H;
         const int head = cc / e.head_dim, dd = cc - head * e.head_dim;
-        bf16* vrow = static_cast<bf16*>(e.vt) + ((int64_t)head * e.head_dim + dd) * e.vt_ld;
+        T* vrow = static_cast<T*>(e.vt) + ((int64_t)head * e.head_dim + dd) * e.vt_ld;
         const float bias = e.bias[n];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-          uint32_t w[8];  // tokens 8 (r / 4) + 4 lg + r % 4 as bf16 pairs
+          if constexpr (sizeof(T) == 4) {  // 4 consecutive tokens are one 16-byte store
 #pragma unroll
-          for (int r = 0; r < 16; r += 2) {
-            const bf16x2 pr = {(bf16)(acc[mb][nb][r] + bias), (bf16)(acc[mb][nb][r + 1] + bias)};
-            w[r / 2] = __builtin_bit_cast(uint32_t, pr);
-          }
-          const int64_t t0 = mw + mb * 32 + 8 * lg;
+            for (int g = 0; g < 4; ++g) {
+              f32x4 v;
 #pragma unroll
-          for (int p = 0; p < 2; ++p) {  // groups 2p (tokens +0..7) and 2p + 1 (+8..15)
-            uint32_t lo[2], hi[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const auto sw = __builtin_amdgcn_permlane32_swap(w[4 * p + h], w[4 * p + 2 + h],
-                                                               false, false);
-              lo[h] = sw[0];
-              hi[h] = sw[1];
+              for (int i = 0; i < 4; ++i) v[i] = acc[mb][nb][4 * g + i] + bias;
+              *reinterpret_cast<f32x4*>(vrow + mrow + mb * 32 + 8 * g) = v;
             }
-            const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
-            *reinterpret_cast<u32x4*>(vrow + t0 + 16 * p) = v;
+          } else {
+            uint32_t w[8];  // tokens 8 (r / 4) + 4 lg + r % 4 as bf16 pairs
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+              const bf16x2 pr = {(bf16)(acc[mb][nb][r] + bias), (bf16)(acc[mb][nb][r + 1] + bias)};
+              w[r / 2] = __builtin_bit_cast(uint32_t, pr);
+            }
+            const int64_t t0 = mw + mb * 32 + 8 * lg;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {  // groups 2p (tokens +0..7) and 2p + 1 (+8..15)
+              uint32_t lo[2], hi[2];
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(w[4 * p + h], w[4 * p + 2 + h],
+                                                                 false, false);
+                lo[h] = sw[0];
+                hi[h] = sw[1];
+              }
+              const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
+              *reinterpret_cast<u32x4*>(vrow + t0 + 16 * p) = v;
+            }
           }
         }
       }
@@ -301,13 +283,13 @@ __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[MB][NB
     }
   }
   const int rows_left = (int)(M - mrow < 32 * MB ? M - mrow : 32 * MB);
-  if constexpr (!ColEpi<KIND, bf16>::kRmw) {
+  if constexpr (!ColEpi<KIND, T>::kRmw) {
     if (full) {
       // The 32-column blocks of a wave fill the two halves of the same
       // 128-byte line of each output row (bf16): store them back to back so
       // the line is complete in the L2 before it can be written back.
       if constexpr (NB == 2) {
-        const ColEpi<KIND, bf16> c0(e, nw + lr, N), c1(e, nw + 32 + lr, N);
+        const ColEpi<KIND, T> c0(e, nw + lr, N), c1(e, nw + 32 + lr, N);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -318,7 +300,7 @@ __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[MB][NB
           }
       } else {
         static_assert(NB == 1, "one or two column blocks per wave");
-        const ColEpi<KIND, bf16> c0(e, nw + lr, N);
+        const ColEpi<KIND, T> c0(e, nw + lr, N);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -331,7 +313,7 @@ __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[MB][NB
     // row per element made the register allocator spill).
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const ColEpi<KIND, bf16> ce(e, nw + nb * 32 + lr, N);
+      const ColEpi<KIND, T> ce(e, nw + nb * 32 + lr, N);
       // The column's bias has landed before the guarded stores: a load still
       // in flight there makes every guarded block wait for all earlier stores.
       asm volatile("" ::"v"(ce.bias));
@@ -348,7 +330,7 @@ __device__ __forceinline__ void tile_epilogue(const Epi& e, f32x16 (&acc)[MB][NB
     constexpr int G = MB % 2 || LOADS < 32 ? 1 : 2;  // row blocks per batch of loads
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const ColEpi<KIND, bf16> ce(e, nw + nb * 32 + lr, N);
+      const ColEpi<KIND, T> ce(e, nw + nb * 32 + lr, N);
       if (full) {
 #pragma unroll
         for (int h = 0; h < MB / G; ++h) {  // a batch of loads in flight, then the stores
@@ -630,7 +612,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_bf16_kernel(const bf16* A
         }
     return;
   }
-  tile_epilogue<KIND, 4, 2>(e, acc, M, N, m0 + wm * 128, n0 + wn * 64, m0 + BM <= M, lane);
+  tile_epilogue<KIND, bf16, 4, 2>(e, acc, M, N, m0 + wm * 128, n0 + wn * 64, m0 + BM <= M, lane);
 }
 
 // The split tiles: partial sums added in split order (deterministic), then
@@ -667,12 +649,88 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_split_reduce_kernel(int64
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[mb][nb][4 * r4 + i] = v[i];
       }
-  tile_epilogue<KIND, 4, 2>(e, acc, M, N, m0 + wm * 128, n0 + wn * 64, m0 + BM <= M, lane);
+  tile_epilogue<KIND, bf16, 4, 2>(e, acc, M, N, m0 + wm * 128, n0 + wn * 64, m0 + BM <= M, lane);
 }
 
-// ------------------------------------------------- bf16 MFMA, few tiles
+// ------------------------------------------------- MFMA, few tiles
 
-// The same product for grids that the 256 x 256 tiles leave mostly idle
+// A DMA wave (w of four) of the ring kernels.  A stage holds SUB K-steps of
+// 128 bytes of the TM x TN tile's operands; DMA i of wave w fills its 1 KB
+// block b = w ND + i: 8 rows of the A tile (the first TM / 8 blocks of a
+// K-step) or of the B tile, 128 bytes each, chunks at the slots of the
+// 256 x 256 kernel's tiles.  Rows past M are clamped.  Stage st goes into
+// buffer st % NST once the MFMA waves have read stage st - NST; barrier st
+// (after the one that admits stage 0) admits stage st + 1.
+template <typename T, int TM, int TN, int SUB, int NST>
+__device__ __forceinline__ void ring_feed(const T* A, const T* Wt, int64_t M, int K, int64_t m0,
+                                          int n0, int w, int lane, const T* ring) {
+  constexpr int kRow = 128 / sizeof(T);         // elements per row and K-step
+  constexpr int kBlk = (TM + TN) / 8;           // 1 KB blocks per K-step
+  constexpr int ND = SUB * kBlk / 4;            // DMAs per wave and stage
+  static_assert(SUB * kBlk % 4 == 0 && NST >= 2 && ND * (NST - 1) <= 63, "ring");
+  const int NS = K / (SUB * kRow);
+  uint64_t base[ND];
+  uint32_t off[ND];
+#pragma unroll
+  for (int i = 0; i < ND; ++i) {
+    const int b = w * ND + i;
+    const int sub = b / kBlk, bb = b % kBlk;
+    const bool is_a = bb < TM / 8;
+    const int r = (is_a ? bb : bb - TM / 8) * 8 + (lane >> 3);
+    const int ch = (lane & 7) ^ ((r >> 1) & 7);
+    const int row = is_a && m0 + r >= M ? (int)(M - 1 - m0) : r;
+    base[i] = uniform_ptr(is_a ? A + m0 * K : Wt + (int64_t)n0 * K);
+    off[i] = (uint32_t)row * (uint32_t)(K * (int)sizeof(T)) + (uint32_t)(sub * 128 + ch * 16);
+  }
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)ring) +
+                        (uint32_t)(w * ND) * 1024u;
+  // fp32 operands may lie at any multiple of 4 bytes (plain loads read them
+  // so): those are copied through registers, complete when issue returns.
+  const bool copy = sizeof(T) == 4 && (((uintptr_t)A | (uintptr_t)Wt) & 15) != 0;
+  auto issue = [&](int st, uint32_t buf) {
+    const uint32_t kb = (uint32_t)st * (SUB * 128);
+    if (copy) {
+      u32x4 v[ND];
+#pragma unroll
+      for (int i = 0; i < ND; ++i)
+        __builtin_memcpy(&v[i], reinterpret_cast<const char*>(base[i] + kb) + off[i], 16);
+      u32x4* dst = reinterpret_cast<u32x4*>(const_cast<T*>(ring)) +
+                   (buf * (uint32_t)(SUB * kBlk) + (uint32_t)(w * ND)) * 64u + lane;
+#pragma unroll
+      for (int i = 0; i < ND; ++i) dst[i * 64] = v[i];
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+      dma16(base[i] + kb, off[i], lds0 + buf * (uint32_t)(SUB * kBlk * 1024) + i * 1024u);
+  };
+  // vmcnt(n), no other counter
+#define RING_WAIT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+#pragma unroll
+  for (int st = 0; st < NST; ++st)
+    if (st < NS) issue(st, st);
+  if (NS >= NST)
+    RING_WAIT(ND * (NST - 1));  // stage 0 landed
+  else
+    RING_WAIT(0);
+  __builtin_amdgcn_s_barrier();
+  uint32_t buf = 0;
+  for (int st = 0; st < NS; ++st) {
+    // stage st + 1 landed: NST - 2 younger stages may be in flight
+    if (st + NST - 1 < NS)
+      RING_WAIT(ND * (NST - 2));
+    else
+      RING_WAIT(0);
+    __builtin_amdgcn_s_barrier();  // stage st read by all: its buffer is free
+    if (st + NST < NS) issue(st + NST, buf);
+    buf = buf + 1 == NST ? 0 : buf + 1;
+  }
+#undef RING_WAIT
+}
+
+// The bf16 product for grids that the 256 x 256 tiles leave mostly idle
 // (short sequences, few rows): TM x TN tiles, WM x WN waves that only read
 // fragments and issue MFMAs, and four waves that only issue the operand
 // DMAs, one on each SIMD beside them.  A K-step of 64 of both operands is
@@ -694,15 +752,15 @@ __global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
   constexpr int kMath = WM * WN;                       // MFMA waves
   constexpr int MB = TM / WM / 32, NB = TN / WN / 32;  // 32 x 32 blocks per wave
   constexpr int kStageElems = (TM + TN) * BK;
-  constexpr int ND = (TM + TN) / 8 / 4;                // 1 KB DMAs per DMA wave and stage
-  static_assert((TM + TN) % 32 == 0 && NST >= 2 && ND * (NST - 1) <= 63, "ring");
   __shared__ __attribute__((aligned(1024))) bf16 ring[NST * kStageElems];
 
   const int tiles_n = N / TN;
   const int64_t tiles_m = (M + TM - 1) / TM;
   int64_t tm;
   int tn;
-  tile_coords<4>(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
+  const int64_t bid = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (bid >= tiles_m * tiles_n) return;
+  tile_coords<4>(xcd_remap(bid, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
   const int64_t m0 = tm * TM;
   const int n0 = tn * TN;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -710,52 +768,7 @@ __global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
   const int NS = K / BK;
 
   if (wave >= kMath) {
-    // DMA i of DMA wave w fills 1 KB block b = w ND + i of a stage: 8 rows of
-    // the A tile (the first TM / 8 blocks) or of the B tile, 128 bytes each,
-    // chunks at the slots of the 256 x 256 kernel's tiles.  Rows past M are
-    // clamped.
-    uint64_t base[ND];
-    uint32_t off[ND];
-#pragma unroll
-    for (int i = 0; i < ND; ++i) {
-      const int b = (wave - kMath) * ND + i;
-      const bool is_a = b < TM / 8;
-      const int r = (is_a ? b : b - TM / 8) * 8 + (lane >> 3);
-      const int ch = (lane & 7) ^ ((r >> 1) & 7);
-      const int row = is_a && m0 + r >= M ? (int)(M - 1 - m0) : r;
-      base[i] = uniform_ptr(is_a ? A + m0 * K : Wt + (int64_t)n0 * K);
-      off[i] = (uint32_t)(row * K + ch * 8) * 2u;
-    }
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)ring) +
-                          (uint32_t)((wave - kMath) * ND) * 1024u;
-    auto issue = [&](int st, uint32_t buf) {
-      const uint32_t kb = (uint32_t)st * (BK * 2);
-#pragma unroll
-      for (int i = 0; i < ND; ++i)
-        dma16(base[i] + kb, off[i], lds0 + buf * (uint32_t)(kStageElems * 2) + i * 1024u);
-    };
-    // vmcnt(n), no other counter
-#define RING_WAIT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
-#pragma unroll
-    for (int st = 0; st < NST; ++st)
-      if (st < NS) issue(st, st);
-    if (NS >= NST)
-      RING_WAIT(ND * (NST - 1));  // stage 0 landed
-    else
-      RING_WAIT(0);
-    __builtin_amdgcn_s_barrier();
-    uint32_t buf = 0;
-    for (int st = 0; st < NS; ++st) {
-      // stage st + 1 landed: NST - 2 younger stages may be in flight
-      if (st + NST - 1 < NS)
-        RING_WAIT(ND * (NST - 2));
-      else
-        RING_WAIT(0);
-      __builtin_amdgcn_s_barrier();  // stage st read by all: its buffer is free
-      if (st + NST < NS) issue(st + NST, buf);
-      buf = buf + 1 == NST ? 0 : buf + 1;
-    }
-#undef RING_WAIT
+    ring_feed<bf16, TM, TN, 1, NST>(A, Wt, M, K, m0, n0, wave - kMath, lane, ring);
     return;
   }
 
@@ -811,57 +824,120 @@ __global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  tile_epilogue<KIND, MB, NB, OCC >= 3 ? 16 : 32>(e, acc, M, N, m0 + wm * (TM / WM),
-                                                 n0 + wn * (TN / WN), m0 + TM <= M, lane);
+  tile_epilogue<KIND, bf16, MB, NB, OCC >= 3 ? 16 : 32>(e, acc, M, N, m0 + wm * (TM / WM),
+                                                       n0 + wn * (TN / WN), m0 + TM <= M, lane);
 }
 
-// ------------------------------------------------------------ fp32 VALU
+// ------------------------------------------------------------ fp32 MFMA
 
-template <int KIND>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
-                                                       const float* __restrict__ Wt, int64_t M,
-                                                       int N, int K, Epi e) {
+// fp32: v_mfma_f32_32x32x2_f32 (products and sums in fp32) on the same ring.
+// A lane's 16-byte fragment of row r holds k = 8 kk + 4 (lane / 32) + 0..3,
+// so MFMA i of a sub-step contracts k = 8 kk + i and 8 kk + 4 + i.  The
+// sub-steps kk = 0..3 of the 32-wide K-steps sum into accumulators of their
+// own, added as ((0 + 1) + (2 + 3)) at the end: with WK = 1 a wave holds all
+// four, with WK = 4 each of four waves holds one and they meet in LDS, so
+// both tiles give the same bits.  Bound by the matrix unit (157 TFLOP/s; an
+// MFMA of 64 cycles per two fragment registers); one wave of the 32 x 32
+// tile has a quarter of the 64 x 64 tile's serial MFMA chain, which is what a
+// launch of few tiles takes.  Against the 64 x 64 VALU kernel before it: a
+// 1013-token fp32 block (H 1024, F 4096) 609 -> 286 us, the 128-token loop
+// (H 256) 890 -> 553 us.
+template <int KIND, int TM, int TN, int WM, int WN, int WK, int SUB, int NST, int OCC>
+__global__ __launch_bounds__(512, OCC) void gemm_f32_kernel(const float* A, const float* Wt,
+                                                            int64_t M, int N, int K, Epi e) {
   if (e.pred && *e.pred == 0) return;
-  __shared__ float As[16][64 + 4];
-  __shared__ float Ws[16][64 + 4];
-  const int64_t m0 = (int64_t)blockIdx.x * 64;
-  const int n0 = blockIdx.y * 64;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const int64_t gm = m0 + lrow;
-    float4 a = gm < M ? *reinterpret_cast<const float4*>(A + gm * K + k0 + lk)
-                      : make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 w = *reinterpret_cast<const float4*>(Wt + (int64_t)(n0 + lrow) * K + k0 + lk);
-    As[lk + 0][lrow] = a.x;
-    As[lk + 1][lrow] = a.y;
-    As[lk + 2][lrow] = a.z;
-    As[lk + 3][lrow] = a.w;
-    Ws[lk + 0][lrow] = w.x;
-    Ws[lk + 1][lrow] = w.y;
-    Ws[lk + 2][lrow] = w.z;
-    Ws[lk + 3][lrow] = w.w;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float4 a4 = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-      float4 w4 = *reinterpret_cast<const float4*>(&Ws[k][tx * 4]);
-      const float av[4] = {a4.x, a4.y, a4.z, a4.w};
-      const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * wv[j];
-    }
-    __syncthreads();
+  constexpr int kRow = 32;           // floats per row and K-step
+  constexpr int NCL = 4 / WK;        // sub-step classes a wave sums
+  constexpr int NSTEP = SUB * NCL;   // sub-steps of a wave per stage
+  constexpr int kStageElems = SUB * (TM + TN) * kRow;
+  static_assert(WM * WN * WK == 4 && TM == 32 * WM && TN == 32 * WN && NSTEP >= 2, "waves");
+  __shared__ __attribute__((aligned(1024))) float ring[NST * kStageElems];
+
+  const int tiles_n = N / TN;
+  const int64_t tiles_m = (M + TM - 1) / TM;
+  int64_t tm;
+  int tn;
+  const int64_t bid = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (bid >= tiles_m * tiles_n) return;
+  tile_coords<4>(xcd_remap(bid, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
+  const int64_t m0 = tm * TM;
+  const int n0 = tn * TN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int NS = K / (SUB * kRow);
+  if (wave >= 4) {
+    ring_feed<float, TM, TN, SUB, NST>(A, Wt, M, K, m0, n0, wave - 4, lane, ring);
+    return;
   }
+
+  const int wk = wave % WK, wm = wave / WK / WN, wn = wave / WK % WN;
+  const int lr = lane & 31, lg = lane >> 5;
+  const int a_rbase = (wm * 32 + lr) * kRow;
+  const int b_rbase = (TM + wn * 32 + lr) * kRow;
+  f32x16 part[NCL];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t m = m0 + ty * 4 + i;
-    if (m >= M) continue;
+  for (int c = 0; c < NCL; ++c)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) epi_elem<KIND, float>(e, m, n0 + tx * 4 + j, N, acc[i][j]);
+    for (int r = 0; r < 16; ++r) part[c][r] = 0.f;
+  f32x4 fa[2], fb[2];
+  auto read_frags = [&](const float* stage, int i) {
+    const int kk = i % NCL * WK + wk;
+    const float* t = stage + (i / NCL) * (TM + TN) * kRow + 4 * ((2 * kk + lg) ^ ((lr >> 1) & 7));
+    fa[i & 1] = *reinterpret_cast<const f32x4*>(t + a_rbase);
+    fb[i & 1] = *reinterpret_cast<const f32x4*>(t + b_rbase);
+  };
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read_frags(ring, 0);
+  int buf = 0;
+  for (int st = 0; st < NS; ++st) {
+    const float* cur = ring + buf * kStageElems;
+    buf = buf + 1 == NST ? 0 : buf + 1;
+    const float* nxt = ring + buf * kStageElems;
+#pragma unroll
+    for (int i = 0; i < NSTEP; ++i) {
+      if (i + 1 < NSTEP) {
+        read_frags(cur, i + 1);
+      } else {
+        // the stage's last fragments have arrived: its buffer may be refilled
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read_frags(nxt, 0);  // after the last stage: read and dropped
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        part[i % NCL] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i & 1][j], fb[i & 1][j],
+                                                             part[i % NCL], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if constexpr (WK == 1) {
+    f32x16 acc[1][1];
+    acc[0][0] = (part[0] + part[1]) + (part[2] + part[3]);
+    tile_epilogue<KIND, float, 1, 1>(e, acc, M, N, m0 + wm * 32, n0 + wn * 32, m0 + TM <= M, lane);
+  } else {
+    static_assert(WK == 4 && 4 * 16 * 64 <= NST * kStageElems, "partial sums fit the ring");
+    // Every DMA has landed and every wave has its last fragments.
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ring[(wk * 16 + r) * 64 + lane] = part[0][r];
+    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+    __builtin_amdgcn_s_barrier();  // the four MFMA waves: the DMA waves have ended
+    asm volatile("" ::: "memory");
+    // wave wk finishes accumulator entries 4 wk .. 4 wk + 3: four rows a lane
+    const ColEpi<KIND, float> ce(e, n0 + lr, N);
+    const int64_t m = m0 + 8 * wk + 4 * lg;
+    float y[4], prev[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* p = ring + (4 * wk + r) * 64 + lane;
+      y[r] = (p[0] + p[16 * 64]) + (p[32 * 64] + p[48 * 64]);
+      prev[r] = ce.old(m + r < M ? m + r : M - 1);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (m + r < M) ce.put_old(m + r, y[r], prev[r]);
   }
 }
 
@@ -930,11 +1006,18 @@ Tile choose_tile(int64_t M, int N, int64_t tiles, int64_t rem, int split) {
   return t;
 }
 
+// Grid of a ring kernel: one workgroup per tile, in two dimensions beyond 2^22
+// (a dimension holds fewer than 2^32 work-items).
+dim3 ring_grid(int64_t tiles) {
+  const int64_t gy = (tiles + (1 << 22) - 1) >> 22;
+  return dim3((unsigned)((tiles + gy - 1) / gy), (unsigned)gy);
+}
+
 template <int KIND, int TM, int TN, int WM, int WN, int NST, int OCC>
 hipError_t launch_ring(int64_t M, int N, int K, const void* a, const void* wt, const Epi& e,
                        hipStream_t s) {
   const int64_t grid = (M + TM - 1) / TM * (N / TN);
-  hipLaunchKernelGGL((gemm_ring_kernel<KIND, TM, TN, WM, WN, NST, OCC>), dim3((unsigned)grid),
+  hipLaunchKernelGGL((gemm_ring_kernel<KIND, TM, TN, WM, WN, NST, OCC>), ring_grid(grid),
                      dim3(64 * (WM * WN + 4)), 0, s, (const bf16*)a, (const bf16*)wt, M, N, K, e);
   return hipGetLastError();
 }
@@ -963,9 +1046,17 @@ hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const 
                          0, s, M, N, e, tiles_main, split);
     }
   } else {
-    dim3 grid((unsigned)((M + 63) / 64), (unsigned)(N / 64));
-    hipLaunchKernelGGL(gemm_f32_kernel<KIND>, grid, dim3(256), 0, s, (const float*)a,
-                       (const float*)wt, M, N, K, e);
+    // 64 x 64 tiles, or 32 x 32 ones where those leave most CUs idle: a round
+    // of 32 x 32 tiles takes a quarter of the time, and about a fifth more
+    // for its shorter K ranges per wave and its reduction.
+    const int64_t cus = cu_count();
+    const int64_t t64 = (M + 63) / 64 * (N / 64), t32 = (M + 31) / 32 * (N / 32);
+    if ((double)((t32 + cus - 1) / cus) * 0.3 < (double)((t64 + cus - 1) / cus))
+      hipLaunchKernelGGL((gemm_f32_kernel<KIND, 32, 32, 1, 1, 4, 2, 4, 4>), ring_grid(t32),
+                         dim3(512), 0, s, (const float*)a, (const float*)wt, M, N, K, e);
+    else
+      hipLaunchKernelGGL((gemm_f32_kernel<KIND, 64, 64, 2, 2, 1, 1, 4, 4>), ring_grid(t64),
+                         dim3(512), 0, s, (const float*)a, (const float*)wt, M, N, K, e);
   }
   return hipGetLastError();
 }

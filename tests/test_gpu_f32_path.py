@@ -57,3 +57,60 @@ def test_attention_f32_masked_keys_have_no_weight(d):
     P.attention(to_dev(q), to_dev(k), to_dev(vt), o)
     ref = O.attention(q[0], k[0][~masked], v[0][~masked])
     np.testing.assert_allclose(to_np(o), ref, rtol=2e-5, atol=2e-5)
+
+
+F32_KINDS = ["bias", "gelu", "gate_residual", "euler", "qkv"]
+
+
+def _linear(P, kind, a, wt, bias, gate, base):
+    M, N = a.shape[0], wt.shape[0]
+    if kind == "qkv":  # 4 heads of 64, Q pre-scaled; returned token-major
+        nh, d = N // 192, 64
+        q, k = (torch.empty((nh, M, d), device="cuda") for _ in range(2))
+        vt = torch.zeros((nh, d, (M + 7) // 8 * 8), device="cuda")
+        P.linear(a, wt, P.ACID_EPI_QKV, bias, q=q, k=k, vt=vt, n_heads=nh, head_dim=d,
+                 q_prescale=True)
+        return torch.cat([q.permute(1, 0, 2).reshape(M, -1), k.permute(1, 0, 2).reshape(M, -1),
+                          vt[:, :, :M].permute(2, 0, 1).reshape(M, -1)], 1)
+    if kind in ("gate_residual", "euler"):
+        out = base[:M].clone()
+        if kind == "euler":
+            P.linear(a, wt, P.ACID_EPI_EULER, bias, out=out, dsigma=-0.25)
+        else:
+            P.linear(a, wt, P.ACID_EPI_GATE_RESIDUAL, bias, gate=gate, out=out)
+        return out
+    out = torch.empty((M, N), device="cuda")
+    P.linear(a, wt, P.ACID_EPI_BIAS_GELU if kind == "gelu" else P.ACID_EPI_BIAS, bias, out=out)
+    return out
+
+
+@pytest.mark.parametrize("kind", F32_KINDS)
+@pytest.mark.parametrize("K", [128, 640])
+def test_linear_f32_tiles_same_bits(kind, K):
+    """32 x 32 tiles (few rows) and 64 x 64 tiles (many) sum in the same
+    order: a call's rows are bit for bit the prefix of a larger call's.  The
+    larger call against fp64; operands at 4-byte alignment give the same."""
+    P = need_gpu()
+    N, full = 768, 2100
+    rng = np.random.default_rng(K)
+    a = to_dev(rng.normal(size=(full, K)))
+    wt = to_dev(rng.normal(size=(N, K)) / np.sqrt(K))
+    bias, gate = to_dev(rng.normal(size=N) * 0.1), to_dev(rng.normal(size=N))
+    base = to_dev(rng.normal(size=(full, N)))
+    whole = _linear(P, kind, a, wt, bias, gate, base)
+    y = to_np(a) @ to_np(wt).T + to_np(bias)
+    acc = K * 2.0 ** -24 * (np.abs(to_np(a)) @ np.abs(to_np(wt)).T + np.abs(to_np(bias)))
+    b, g = to_np(base), to_np(gate)
+    ref, tol = {"bias": (y, acc), "gelu": (O.gelu_tanh(y), 1.13 * acc + 1e-6),
+                "gate_residual": (b + g * y, np.abs(g) * acc + 2.0 ** -22 * (np.abs(b) + np.abs(g * y))),
+                "euler": (b - 0.25 * y, 0.25 * acc + 2.0 ** -22 * (np.abs(b) + np.abs(y))),
+                "qkv": (y * np.where(np.arange(N) < 256, P.q_scale(64), 1.0), acc)}[kind]
+    assert_elementwise(to_np(whole), ref, tol, 2.0 ** -22, f"fp32 {kind} K={K}")
+    for m in (1, 31, 32, 33, 130, 700, 2049):
+        assert torch.equal(_linear(P, kind, a[:m].contiguous(), wt, bias, gate, base), whole[:m]), m
+    flat = torch.empty(full * K + 1, device="cuda")
+    off = flat[1:].view(full, K)
+    off.copy_(a)
+    assert off.data_ptr() % 16 == 4
+    assert torch.equal(_linear(P, kind, off, wt, bias, gate, base), whole)
+    assert torch.equal(_linear(P, kind, off[:45], wt, bias, gate, base), whole[:45])
