@@ -123,11 +123,12 @@ hipError_t launch_transpose_convert(const float* src, int64_t in, int64_t out, i
 hipError_t launch_sinusoid(const float* sigmas_host, int n, int freq_dim, float* e,
                            hipStream_t s);
 // Y[s][n] = act_out( X[s][:] . W[:, n] + b[n] ) (act_out: 0 none, 1 SiLU), batched over `batch`
-// groups with element strides for W, b and the output column offset.
-hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float* W,
+// groups with element strides for W, b and the output column offset; W's
+// rows are ldw elements apart, N is a multiple of 128.
+hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float* W, int ldw,
                               int N, const float* b, float* Y, int64_t ldy, int act_out,
-                              int batch, int64_t w_stride, int64_t b_stride,
-                              int64_t y_stride, hipStream_t s);
+                              int batch, int64_t w_stride, int64_t b_stride, int64_t y_stride,
+                              hipStream_t s);
 
 // GEMMs (gemm.hip)
 // split_ws: for bf16, a workspace of kGemmSplitWsBytes with which grids whose

@@ -310,17 +310,17 @@ acid_status modulation_table(acid_model* m, const float* sigmas, int n, float* t
   return run(m, ACID_K_TEMB, s, "timestep modulation", [&]() {
     hipError_t err = launch_sinusoid(sigmas, n, Ft, e, s);
     if (err == hipSuccess)
-      err = launch_skinny_gemm(e, Ft, n, Ft, m->wp(m->wl.temb_w1), H, m->wp(m->wl.temb_b1), hid,
+      err = launch_skinny_gemm(e, Ft, n, Ft, m->wp(m->wl.temb_w1), H, H, m->wp(m->wl.temb_b1), hid,
                                H, 1, 1, 0, 0, 0, s);
     if (err == hipSuccess)
-      err = launch_skinny_gemm(hid, H, n, H, m->wp(m->wl.temb_w2), H, m->wp(m->wl.temb_b2), u, H,
-                               1, 1, 0, 0, 0, s);
+      err = launch_skinny_gemm(hid, H, n, H, m->wp(m->wl.temb_w2), H, H, m->wp(m->wl.temb_b2), u,
+                               H, 1, 1, 0, 0, 0, s);
     if (err == hipSuccess)
-      err = launch_skinny_gemm(u, H, n, H, m->bp(0, m->wl.ada_w), 6 * H, m->bp(0, m->wl.ada_b),
-                               table, m->rowsz(), 0, c.n_blocks, bstride, bstride,
+      err = launch_skinny_gemm(u, H, n, H, m->bp(0, m->wl.ada_w), 6 * H, 6 * H,
+                               m->bp(0, m->wl.ada_b), table, m->rowsz(), 0, c.n_blocks, bstride, bstride,
                                6 * (int64_t)H, s);
     if (err == hipSuccess)
-      err = launch_skinny_gemm(u, H, n, H, m->wp(m->wl.head_ada_w), 2 * H,
+      err = launch_skinny_gemm(u, H, n, H, m->wp(m->wl.head_ada_w), 2 * H, 2 * H,
                                m->wp(m->wl.head_ada_b), table + 6 * (int64_t)c.n_blocks * H,
                                m->rowsz(), 0, 1, 0, 0, 0, s);
     return err;

@@ -29,91 +29,128 @@ __global__ void sinusoid_kernel(SigmaPack sig, int n, int freq_dim, float* __res
   }
 }
 
-constexpr int kKChunk = 64;   // K rows of X staged per LDS round
-constexpr int kColsPerBlock = 128;  // two columns per lane, 64 lanes
-
-// Y[s][n] = act(sum_k X[s][k] W[k][n] + b[n]) for up to R rows s per block.
-// Lane l of every wave owns columns 2l, 2l+1 of the block's 128; the four
-// waves split K (wave w takes the rows k = 4j + w of each staged chunk), so
-// each wave keeps 16 independent float2 loads of W in flight per chunk and
-// W is read once for all R rows.  The waves' partial sums meet in LDS and
-// are added in a fixed order (deterministic).
-template <int R>
-__global__ __launch_bounds__(256) void skinny_gemm_kernel(
-    const float* __restrict__ X, int ldx, int S, int K, const float* __restrict__ W, int N,
+// Y[s][n] = act(sum_k X[s][k] W[k][n] + b[n]) for 32 RB rows s and 32 CB
+// columns n per workgroup, on the fp32 matrix instruction
+// (v_mfma_f32_32x32x2_f32).  Bound by reading W once (1.7 GB at the Wan-1.3B
+// shape).  The NW waves split K in groups of 8 (wave w takes groups w,
+// w + NW, ...): lane (half-wave h, index l) loads X[l][8 g + 4 h ..+3] and
+// W[8 g + 4 h + i][n0 + CB l ..+CB-1], so MFMA i of a group contracts
+// k = 8 g + i and 8 g + 4 + i, and one load of W is the operand of CB column
+// blocks.  Two or three groups are kept in flight per wave.  The waves' partial sums
+// meet in LDS and are added in wave order (deterministic, and independent of
+// RB: a row's values do not depend on how many rows the call holds).
+// 50 rows x 30 x (1536 x 9216): the 16-rows-at-a-time VALU kernel took 1277
+// us, this one 545 (MFMAs on rows padded to 64: 346; one row: 316 us, 5.4
+// TB/s); the table with its three small products 1793 -> 594 us.  Two column
+// blocks per workgroup ran 18% slower, an eight-way split 14%.
+template <int RB, int CB, int NW>
+__global__ __launch_bounds__(64 * NW, CB == 4 ? 2 : 4) void skinny_gemm_kernel(
+    const float* __restrict__ X, int ldx, int S, int K, const float* __restrict__ W, int ldw,
     const float* __restrict__ bias, float* __restrict__ Y, int64_t ldy, int act_out,
     int64_t w_stride, int64_t b_stride, int64_t y_stride) {
-  // X chunk [kKChunk][R] during the K loop; [4 waves][16 rows][128 cols]
-  // partial sums during the reduction (32 KB).
-  __shared__ __attribute__((aligned(16))) float lds[4 * 16 * kColsPerBlock];
-  static_assert(kKChunk * R <= 4 * 16 * kColsPerBlock, "X chunk must fit");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cb = blockIdx.x * kColsPerBlock;
-  const int c = cb + 2 * lane;
-  const int g = blockIdx.y;
-  const int s0 = blockIdx.z * R;
-  const int rows = min(R, S - s0);
-  const float* Wg = W + g * w_stride;
-  const float* bg = bias + g * b_stride;
-  float* Yg = Y + g * y_stride;
-  const bool col_ok = c < N;  // N is even, so c + 1 < N too
-  float acc[R][2];
+  typedef float wvec __attribute__((ext_vector_type(CB)));
+  constexpr int D = CB == 4 ? 2 : 3;  // groups in flight
+  __shared__ wvec lds[NW * 16 * 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lg = lane >> 5;
+  const int n0 = blockIdx.x * 32 * CB, g = blockIdx.y, s0 = blockIdx.z * 32 * RB;
+  const float* wp = W + g * w_stride + (int64_t)(4 * lg) * ldw + n0 + CB * lr;
+  const float* xp[RB];
 #pragma unroll
-  for (int r = 0; r < R; ++r) acc[r][0] = acc[r][1] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += kKChunk) {
-    const int kend = min(kKChunk, K - k0);
-    __syncthreads();
-    for (int idx = tid; idx < kKChunk * R; idx += 256) {
-      const int kk = idx / R, r = idx % R;
-      lds[idx] = (r < rows && kk < kend) ? X[(int64_t)(s0 + r) * ldx + k0 + kk] : 0.f;
-    }
-    __syncthreads();
-    if (col_ok) {
-      float2 w[kKChunk / 4];
-#pragma unroll
-      for (int j = 0; j < kKChunk / 4; ++j) {
-        const int kk = 4 * j + wave;
-        w[j] = kk < kend ? *reinterpret_cast<const float2*>(Wg + (int64_t)(k0 + kk) * N + c)
-                         : make_float2(0.f, 0.f);
-      }
-#pragma unroll
-      for (int j = 0; j < kKChunk / 4; ++j) {
-        const float* xk = lds + (4 * j + wave) * R;  // wave-uniform: broadcast reads
-#pragma unroll
-        for (int r = 0; r < R; r += 4) {
-          const float4 xv = *reinterpret_cast<const float4*>(xk + r);
-          acc[r + 0][0] += xv.x * w[j].x;
-          acc[r + 0][1] += xv.x * w[j].y;
-          acc[r + 1][0] += xv.y * w[j].x;
-          acc[r + 1][1] += xv.y * w[j].y;
-          acc[r + 2][0] += xv.z * w[j].x;
-          acc[r + 2][1] += xv.z * w[j].y;
-          acc[r + 3][0] += xv.w * w[j].x;
-          acc[r + 3][1] += xv.w * w[j].y;
-        }
-      }
-    }
+  for (int rb = 0; rb < RB; ++rb) {  // rows past S repeat the last and are not stored
+    const int row = s0 + 32 * rb + lr;
+    xp[rb] = X + (int64_t)(row < S ? row : S - 1) * ldx + 4 * lg;
   }
-  // Reduction over the four waves, 16 rows at a time.
+  struct Frag {
+    f32x4 x[RB];
+    wvec w[4];
+  };
+  f32x16 acc[RB][CB];
 #pragma unroll
-  for (int rr = 0; rr < R; rr += 16) {
-    __syncthreads();
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      *reinterpret_cast<float2*>(lds + (wave * 16 + r) * kColsPerBlock + 2 * lane) =
-          make_float2(acc[rr + r][0], acc[rr + r][1]);
-    __syncthreads();
-    for (int o = tid; o < 16 * kColsPerBlock; o += 256) {
-      const int r = o / kColsPerBlock, cc = o % kColsPerBlock;
-      const int col = cb + cc;
-      if (rr + r < rows && col < N) {
-        const float* p = lds + r * kColsPerBlock + cc;
-        float y = ((p[0] + p[16 * kColsPerBlock]) + p[32 * kColsPerBlock]) +
-                  p[48 * kColsPerBlock];
-        y += bg[col];
-        if (act_out == 1) y = silu(y);
-        Yg[(int64_t)(s0 + rr + r) * ldy + col] = y;
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[rb][cb][r] = 0.f;
+  auto load = [&](Frag& f, int grp) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      f.w[i] = *reinterpret_cast<const wvec*>(wp + (int64_t)(8 * grp + i) * ldw);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) f.x[rb] = *reinterpret_cast<const f32x4*>(xp[rb] + 8 * grp);
+  };
+  auto mma = [&](const Frag& f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+          acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.x[rb][i], f.w[i][cb], acc[rb][cb],
+                                                             0, 0, 0);
+  };
+  const int full = K / 8;
+  const int cnt = wave < full ? (full - 1 - wave) / NW + 1 : 0;  // this wave's whole groups
+  if (cnt > 0) {
+    Frag f[D];
+    auto grp = [&](int j) { return wave + min(j, cnt - 1) * NW; };  // past the last: read again
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(f[d], grp(d));
+    int j = 0;
+    // No branch between a group's MFMAs and its refill: with one, the
+    // compiler waits for every load in flight at the loop's top.
+    for (; j + D <= cnt; j += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        mma(f[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        load(f[d], grp(j + d + D));
+        __builtin_amdgcn_sched_barrier(0);
       }
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (j + d < cnt) mma(f[d]);
+  }
+  if (K % 8 != 0 && wave == full % NW) {  // the ragged last group, element by element
+    Frag f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool in = 8 * full + 4 * lg + i < K;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+        f.w[i][cb] = in ? wp[(int64_t)(8 * full + i) * ldw + cb] : 0.f;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) f.x[rb][i] = in ? xp[rb][8 * full + i] : 0.f;
+    }
+    mma(f);
+  }
+  const wvec bv = *reinterpret_cast<const wvec*>(bias + g * b_stride + n0 + CB * lr);
+  float* Yg = Y + g * y_stride + n0 + CB * lr;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    if (rb) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      wvec v;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) v[cb] = acc[rb][cb][r];
+      lds[(wave * 16 + r) * 64 + lane] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = wave; r < 16; r += NW) {  // accumulator entry r: row 8 (r / 4) + 4 h + r % 4
+      wvec y = lds[r * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) y += lds[(w * 16 + r) * 64 + lane];
+      y += bv;
+      if (act_out == 1) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) y[cb] = silu(y[cb]);
+      }
+      const int row = s0 + 32 * rb + 8 * (r >> 2) + 4 * lg + (r & 3);
+      if (row < S) *reinterpret_cast<wvec*>(Yg + (int64_t)row * ldy) = y;
     }
   }
 }
@@ -134,24 +171,31 @@ hipError_t launch_sinusoid(const float* sigmas_host, int n, int freq_dim, float*
   return hipSuccess;
 }
 
-hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float* W, int N,
-                              const float* b, float* Y, int64_t ldy, int act_out, int batch,
-                              int64_t w_stride, int64_t b_stride, int64_t y_stride,
+hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float* W, int ldw,
+                              int N, const float* b, float* Y, int64_t ldy, int act_out,
+                              int batch, int64_t w_stride, int64_t b_stride, int64_t y_stride,
                               hipStream_t s) {
   if (S == 0 || batch == 0) return hipSuccess;
-  if (N % 2 != 0 || ((uintptr_t)W % 8) != 0 || (w_stride % 2) != 0)
-    return hipErrorInvalidValue;  // float2 loads of W
-  const unsigned cols = (unsigned)((N + kColsPerBlock - 1) / kColsPerBlock);
-#define SKINNY(R)                                                                            \
-  hipLaunchKernelGGL(skinny_gemm_kernel<R>, dim3(cols, (unsigned)batch, (unsigned)((S + R - 1) / R)), \
-                     dim3(256), 0, s, X, ldx, S, K, W, N, b, Y, ldy, act_out, w_stride,     \
+  if (N % 128 != 0 || ((uintptr_t)W % 16) != 0 || (w_stride % 4) != 0 || (ldw % 4) != 0 ||
+      ((uintptr_t)b % 16) != 0 || (b_stride % 4) != 0)
+    return hipErrorInvalidValue;  // 16-byte loads of W and b (Y may lie at any float)
+#define SKINNY(RB, CB, NW)                                                                      \
+  hipLaunchKernelGGL((skinny_gemm_kernel<RB, CB, NW>),                                          \
+                     dim3((unsigned)(N / (32 * CB)), (unsigned)batch,                           \
+                          (unsigned)((S + 32 * RB - 1) / (32 * RB))),                           \
+                     dim3(64 * NW), 0, s, X, ldx, S, K, W, ldw, b, Y, ldy, act_out, w_stride,   \
                      b_stride, y_stride)
-  if (S <= 16)
-    SKINNY(16);
+  // 128 columns and a four-way K split per workgroup where that gives the
+  // CUs a workgroup each (then 64 rows share a read of W); otherwise 32
+  // columns, 32 rows and a sixteen-way split: a 1536 x 1536 product of 50
+  // rows is 12 workgroups of the one and 96 of the other.  The choice does
+  // not look at S, so that a row's sums do not either.
+  if ((int64_t)(N / 128) * batch < 256)
+    SKINNY(1, 1, 16);
   else if (S <= 32)
-    SKINNY(32);
+    SKINNY(1, 4, 4);
   else
-    SKINNY(64);
+    SKINNY(2, 4, 4);
 #undef SKINNY
   return hipGetLastError();
 }
