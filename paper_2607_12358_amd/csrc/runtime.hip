@@ -299,30 +299,54 @@ acid_status run(acid_model* m, int cls, hipStream_t s, const char* what, F&& f) 
 
 // ------------------------------------------------------------ model pieces
 
-acid_status modulation_table(acid_model* m, const float* sigmas, int n, float* table,
-                             hipStream_t s) {
-  const acid_dit_config& c = m->cfg;
-  const int H = c.hidden, Ft = c.freq_dim;
+// u = the timestep conditioning (two SiLU products of the sinusoid) of n
+// noise levels, in the workspace.
+hipError_t timestep_conditioning(acid_model* m, const float* sigmas, int n, hipStream_t s) {
+  const int H = m->cfg.hidden, Ft = m->cfg.freq_dim;
   float* e = m->kp(m->kl.temb_e);
   float* hid = m->kp(m->kl.temb_hid);
   float* u = m->kp(m->kl.temb_u);
+  hipError_t err = launch_sinusoid(sigmas, n, Ft, e, s);
+  if (err == hipSuccess)
+    err = launch_skinny_gemm(e, Ft, n, Ft, m->wp(m->wl.temb_w1), H, H, m->wp(m->wl.temb_b1), hid,
+                             H, 1, 1, 0, 0, 0, s);
+  if (err == hipSuccess)
+    err = launch_skinny_gemm(hid, H, n, H, m->wp(m->wl.temb_w2), H, H, m->wp(m->wl.temb_b2), u, H,
+                             1, 1, 0, 0, 0, s);
+  return err;
+}
+
+acid_status modulation_table(acid_model* m, const float* sigmas, int n, float* table,
+                             hipStream_t s) {
+  const acid_dit_config& c = m->cfg;
+  const int H = c.hidden;
+  const float* u = m->kp(m->kl.temb_u);
   const int64_t bstride = (int64_t)(m->wl.blk_stride / 4);
   return run(m, ACID_K_TEMB, s, "timestep modulation", [&]() {
-    hipError_t err = launch_sinusoid(sigmas, n, Ft, e, s);
-    if (err == hipSuccess)
-      err = launch_skinny_gemm(e, Ft, n, Ft, m->wp(m->wl.temb_w1), H, H, m->wp(m->wl.temb_b1), hid,
-                               H, 1, 1, 0, 0, 0, s);
-    if (err == hipSuccess)
-      err = launch_skinny_gemm(hid, H, n, H, m->wp(m->wl.temb_w2), H, H, m->wp(m->wl.temb_b2), u,
-                               H, 1, 1, 0, 0, 0, s);
+    hipError_t err = timestep_conditioning(m, sigmas, n, s);
     if (err == hipSuccess)
       err = launch_skinny_gemm(u, H, n, H, m->bp(0, m->wl.ada_w), 6 * H, 6 * H,
-                               m->bp(0, m->wl.ada_b), table, m->rowsz(), 0, c.n_blocks, bstride, bstride,
-                               6 * (int64_t)H, s);
+                               m->bp(0, m->wl.ada_b), table, m->rowsz(), 0, c.n_blocks, bstride,
+                               bstride, 6 * (int64_t)H, s);
     if (err == hipSuccess)
       err = launch_skinny_gemm(u, H, n, H, m->wp(m->wl.head_ada_w), 2 * H, 2 * H,
                                m->wp(m->wl.head_ada_b), table + 6 * (int64_t)c.n_blocks * H,
                                m->rowsz(), 0, 1, 0, 0, 0, s);
+    return err;
+  });
+}
+
+// Block 0's (shift1, scale1) at one noise level, the pair that TEMNI uses:
+// the first 2 H of the 6 H columns of its adaLN weights, of which a whole
+// row of the table reads n_blocks x 6 H (1.7 GB at the Wan-1.3B shape, 0.35
+// ms of a 0.48 ms drift signal, against 19 MB).
+acid_status temni_pair(acid_model* m, float sigma, float* pair, hipStream_t s) {
+  const int H = m->cfg.hidden;
+  return run(m, ACID_K_TEMB, s, "timestep modulation", [&]() {
+    hipError_t err = timestep_conditioning(m, &sigma, 1, s);
+    if (err == hipSuccess)
+      err = launch_skinny_gemm(m->kp(m->kl.temb_u), H, 1, H, m->bp(0, m->wl.ada_w), 6 * H, 2 * H,
+                               m->bp(0, m->wl.ada_b), pair, 2 * H, 0, 1, 0, 0, 0, s);
     return err;
   });
 }
@@ -1247,7 +1271,7 @@ acid_status acid_drift_signal(acid_model* m, const float* x_dev, float sigma,
                               hipStream_t stream) {
   if (!m || !x_dev || !m_cur_dev || !s_out) return set_error(ACID_ERR_INVALID_ARG, "NULL argument");
   float* row = m->kp(m->kl.modtab);
-  ACID_TRY(modulation_table(m, &sigma, 1, row, stream));
+  ACID_TRY(temni_pair(m, sigma, row, stream));
   ACID_TRY(drift(m, row, x_dev, m_prev_dev, m_cur_dev, stream));
   if (!m_prev_dev) {
     ACID_HIP(hipStreamSynchronize(stream));
