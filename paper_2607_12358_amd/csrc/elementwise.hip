@@ -27,6 +27,11 @@ __device__ __forceinline__ void store4(bf16* out, int64_t idx4, float4 y) {
   reinterpret_cast<bf16x4*>(out)[idx4] = v;
 }
 
+__device__ __forceinline__ float4 load4_nt(const float4* p) {
+  const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // Chunk c of a row as this lane reads and writes it.  Indices past the
 // row's n4 chunks are clamped to its last chunk, so every load and store is
 // unconditional (a load under a branch that also uses it makes the wave
@@ -193,14 +198,38 @@ __global__ __launch_bounds__(256) void temni_drift_kernel(
   }
 }
 
+// Sums of u and v over a block of 1024 threads, in thread 0: a fixed
+// butterfly within each wave, then over the 16 waves' sums (two barriers; a
+// binary tree in LDS took ten and 2-3 us more).
+__device__ __forceinline__ void block_sum2_f64(double& u, double& v) {
+  __shared__ double su[16], sv[16];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    u += __shfl_xor(u, off, 64);
+    v += __shfl_xor(v, off, 64);
+  }
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (lane == 0) {
+    su[w] = u;
+    sv[w] = v;
+  }
+  __syncthreads();
+  u = su[lane & 15];
+  v = sv[lane & 15];
+#pragma unroll
+  for (int off = 8; off > 0; off >>= 1) {
+    u += __shfl_xor(u, off, 64);
+    v += __shfl_xor(v, off, 64);
+  }
+}
+
 // One block of 1024 threads over G partial pairs: thread t adds pairs t,
-// t + 1024, ... in that order (eight loads in flight at a time), then a
-// fixed binary tree in LDS.  Deterministic for a given G.
+// t + 1024, ... in that order (eight loads in flight at a time), then the
+// block sum above.  Deterministic for a given G.
 __global__ __launch_bounds__(1024) void drift_finalize_kernel(const double* __restrict__ part,
                                                               int64_t G,
                                                               double* __restrict__ out) {
   constexpr int kT = 1024, kU = 8;
-  __shared__ double sn[kT], sd[kT];
   const int t = threadIdx.x;
   const double2* p2 = reinterpret_cast<const double2*>(part);
   double n = 0.0, d = 0.0;
@@ -220,24 +249,15 @@ __global__ __launch_bounds__(1024) void drift_finalize_kernel(const double* __re
     n += v.x;
     d += v.y;
   }
-  sn[t] = n;
-  sd[t] = d;
-  __syncthreads();
-  for (int w = kT / 2; w > 0; w >>= 1) {
-    if (t < w) {
-      sn[t] += sn[t + w];
-      sd[t] += sd[t + w];
-    }
-    __syncthreads();
-  }
+  block_sum2_f64(n, d);
   if (t == 0) {
-    double num = sn[0], den = sd[0], s;
-    if (den == 0.0)
-      s = (num == 0.0) ? 0.0 : __builtin_inf();
+    double s;
+    if (d == 0.0)
+      s = (n == 0.0) ? 0.0 : __builtin_inf();
     else
-      s = num / den;
-    out[0] = num;
-    out[1] = den;
+      s = n / d;
+    out[0] = n;
+    out[1] = d;
     out[2] = s;
   }
 }
@@ -404,7 +424,7 @@ __device__ __forceinline__ double block_sum_f64(double v, double* lds) {
   return t;
 }
 
-template <bool HAS_B, bool HAS_C>
+template <bool HAS_B, bool HAS_C, bool NT>
 __global__ __launch_bounds__(256) void l1_partials_kernel(const float* __restrict__ a,
                                                           const float* __restrict__ b,
                                                           const float* __restrict__ c,
@@ -418,18 +438,16 @@ __global__ __launch_bounds__(256) void l1_partials_kernel(const float* __restric
   const float4* b4 = reinterpret_cast<const float4*>(b);
   const float4* c4 = reinterpret_cast<const float4*>(c);
   double s0 = 0.0, s1 = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-    float4 av = a4[i];
-    if (HAS_B) {
-      const float4 bv = b4[i];
-      av = make_float4(av.x - bv.x, av.y - bv.y, av.z - bv.z, av.w - bv.w);
-    }
+  auto add = [&](float4 av, float4 bv, float4 cv) {
+    if (HAS_B) av = make_float4(av.x - bv.x, av.y - bv.y, av.z - bv.z, av.w - bv.w);
     s0 += ((double)fabsf(av.x) + (double)fabsf(av.y)) + ((double)fabsf(av.z) + (double)fabsf(av.w));
-    if (HAS_C) {
-      const float4 cv = c4[i];
+    if (HAS_C)
       s1 += ((double)fabsf(cv.x) + (double)fabsf(cv.y)) + ((double)fabsf(cv.z) + (double)fabsf(cv.w));
-    }
-  }
+  };
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto ld = [](const float4* p) { return NT ? load4_nt(p) : *p; };
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride)
+    add(ld(a4 + i), HAS_B ? ld(b4 + i) : zero, HAS_C ? ld(c4 + i) : zero);
   if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {
     const int64_t i = n4 * 4 + threadIdx.x;
     s0 += (double)fabsf(HAS_B ? a[i] - b[i] : a[i]);
@@ -443,31 +461,21 @@ __global__ __launch_bounds__(256) void l1_partials_kernel(const float* __restric
   }
 }
 
-// Fixed-order sum of G partial pairs: out[0], out[1].
+// Fixed-order sum of G <= 1024 partial pairs: out[0], out[1].
 __global__ __launch_bounds__(1024) void l1_finalize_kernel(const double* __restrict__ part, int G,
                                                            double* __restrict__ out,
                                                            const int32_t* __restrict__ pred) {
   if (pred && *pred == 0) return;
-  __shared__ double s0[1024], s1[1024];
   const int t = threadIdx.x;
   double u = 0.0, w = 0.0;
-  for (int g = t; g < G; g += 1024) {
-    u += part[2 * g];
-    w += part[2 * g + 1];
+  if (t < G) {
+    u = part[2 * t];
+    w = part[2 * t + 1];
   }
-  s0[t] = u;
-  s1[t] = w;
-  __syncthreads();
-  for (int k = 512; k > 0; k >>= 1) {
-    if (t < k) {
-      s0[t] += s0[t + k];
-      s1[t] += s1[t + k];
-    }
-    __syncthreads();
-  }
+  block_sum2_f64(u, w);
   if (t == 0) {
-    out[0] = s0[0];
-    out[1] = s1[0];
+    out[0] = u;
+    out[1] = w;
   }
 }
 
@@ -660,8 +668,21 @@ hipError_t launch_l1_norms(const float* a, const float* b, const float* c, int64
                            double* partials, int max_groups, double* out, hipStream_t s,
                            const int32_t* pred) {
   const int G = l1_grid(n, max_groups);
-#define L1K(HB, HC) \
-  hipLaunchKernelGGL((l1_partials_kernel<HB, HC>), dim3(G), dim3(256), 0, s, a, b, c, n, partials, pred)
+  // Non-temporal loads where the streams are too large to be found in the
+  // caches again: three of 201 MB 130 -> 118 us (5.1 TB/s; 330 -> 305 us with
+  // the reuse kernel after it), of 49 MB 5% faster, of 12 MB 4% slower.  Loads
+  // of two or four iterations in flight, a contiguous range per workgroup, or
+  // 512 and 1024 threads ran the same or slower.
+  const bool nt = n * (1 + (b != nullptr) + (c != nullptr)) > ((int64_t)16 << 20);
+#define L1K(HB, HC)                                                                              \
+  do {                                                                                           \
+    if (nt)                                                                                      \
+      hipLaunchKernelGGL((l1_partials_kernel<HB, HC, true>), dim3(G), dim3(256), 0, s, a, b, c,  \
+                         n, partials, pred);                                                     \
+    else                                                                                         \
+      hipLaunchKernelGGL((l1_partials_kernel<HB, HC, false>), dim3(G), dim3(256), 0, s, a, b, c, \
+                         n, partials, pred);                                                     \
+  } while (0)
   if (b && c) L1K(true, true);
   else if (b) L1K(true, false);
   else if (c) L1K(false, true);
