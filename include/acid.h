@@ -190,7 +190,9 @@ acid_status acid_tensor_shape(const acid_dit_config* cfg, int32_t id,
 
 /* Binds a model to a caller-allocated weight arena (acid_weights_bytes, any
  * 256-byte-aligned device allocation) and workspace (acid_workspace_bytes for
- * max_steps).  Allocates only the small host-side struct. */
+ * max_steps).  Allocates only the small host-side struct; the process's first
+ * model also allocates one page of pinned host memory, which all models share
+ * for the signals returned to the host. */
 acid_status acid_model_create(const acid_dit_config* cfg, void* weights_dev,
                               void* workspace_dev, int32_t max_steps,
                               acid_model** out);

@@ -85,9 +85,10 @@ hipError_t launch_temni_drift(const float* x, int64_t rows, int H, const float* 
                               double* partials, hipStream_t s);
 int64_t drift_partial_count(int64_t rows);
 // Fixed-order reduction of the (num, den) pairs of launch_temni_drift over
-// `rows` rows -> out[0]=num, out[1]=den, out[2]=s.
+// `rows` rows -> out[0]=num, out[1]=den, out[2]=s; host (pinned host memory
+// the device can write, or null) receives s too.
 hipError_t launch_drift_finalize(const double* partials, int64_t rows, double* out,
-                                 hipStream_t s);
+                                 hipStream_t s, double* host = nullptr);
 // With `flag` (a device int32) the operation is STORE if *flag, else APPLY;
 // without it, op, skipped when predicated off.
 hipError_t launch_cache(int op, const float* x, float* h, float* r, int64_t n,
@@ -108,13 +109,14 @@ hipError_t launch_easycache_rate(const double* res, double* ec, const int32_t* p
 // Algorithm 1 over a signal sequence on the device.
 hipError_t launch_gate_sequence(const double* sig, int n, const acid_gate_params& p,
                                 acid_step_trace* tr, hipStream_t s);
-// fp32 [in][out] -> [out][in] in dtype
+// out[0] = sum |a - b| (|a| without b), out[1] = sum |c| (0 without c); host
+// (pinned host memory the device can write, or null) receives both too.
 hipError_t launch_l1_norms(const float* a, const float* b, const float* c, int64_t n,
                            double* partials, int max_groups, double* out, hipStream_t s,
-                           const int32_t* pred = nullptr);
+                           const int32_t* pred = nullptr, double* host = nullptr);
 hipError_t launch_easycache_reuse(float* x, float* xp, float* v, const float* d, int64_t n,
                                   float dsig, hipStream_t s, const int32_t* pred = nullptr);
-// dst row o at dst + o * ldd (ldd 0: in).
+// fp32 [in][out] -> [out][in] in dtype; dst row o at dst + o * ldd (ldd 0: in).
 hipError_t launch_transpose_convert(const float* src, int64_t in, int64_t out, int dtype,
                                     void* dst, hipStream_t s, int64_t ldd = 0);
 

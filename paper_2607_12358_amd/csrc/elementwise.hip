@@ -228,7 +228,8 @@ __device__ __forceinline__ void block_sum2_f64(double& u, double& v) {
 // block sum above.  Deterministic for a given G.
 __global__ __launch_bounds__(1024) void drift_finalize_kernel(const double* __restrict__ part,
                                                               int64_t G,
-                                                              double* __restrict__ out) {
+                                                              double* __restrict__ out,
+                                                              double* host) {
   constexpr int kT = 1024, kU = 8;
   const int t = threadIdx.x;
   const double2* p2 = reinterpret_cast<const double2*>(part);
@@ -259,6 +260,7 @@ __global__ __launch_bounds__(1024) void drift_finalize_kernel(const double* __re
     out[0] = n;
     out[1] = d;
     out[2] = s;
+    if (host) host[0] = s;
   }
 }
 
@@ -463,7 +465,7 @@ __global__ __launch_bounds__(256) void l1_partials_kernel(const float* __restric
 
 // Fixed-order sum of G <= 1024 partial pairs: out[0], out[1].
 __global__ __launch_bounds__(1024) void l1_finalize_kernel(const double* __restrict__ part, int G,
-                                                           double* __restrict__ out,
+                                                           double* __restrict__ out, double* host,
                                                            const int32_t* __restrict__ pred) {
   if (pred && *pred == 0) return;
   const int t = threadIdx.x;
@@ -476,6 +478,10 @@ __global__ __launch_bounds__(1024) void l1_finalize_kernel(const double* __restr
   if (t == 0) {
     out[0] = u;
     out[1] = w;
+    if (host) {
+      host[0] = u;
+      host[1] = w;
+    }
   }
 }
 
@@ -588,9 +594,9 @@ hipError_t launch_temni_drift(const float* x, int64_t rows, int H, const float* 
 int64_t drift_partial_count(int64_t rows) { return (rows + kRowsPerBlock - 1) / kRowsPerBlock; }
 
 hipError_t launch_drift_finalize(const double* partials, int64_t rows, double* out,
-                                 hipStream_t s) {
+                                 hipStream_t s, double* host) {
   hipLaunchKernelGGL(drift_finalize_kernel, dim3(1), dim3(1024), 0, s, partials,
-                     drift_partial_count(rows), out);
+                     drift_partial_count(rows), out, host);
   return hipGetLastError();
 }
 
@@ -666,7 +672,7 @@ hipError_t launch_gate_sequence(const double* sig, int n, const acid_gate_params
 
 hipError_t launch_l1_norms(const float* a, const float* b, const float* c, int64_t n,
                            double* partials, int max_groups, double* out, hipStream_t s,
-                           const int32_t* pred) {
+                           const int32_t* pred, double* host) {
   const int G = l1_grid(n, max_groups);
   // Non-temporal loads where the streams are too large to be found in the
   // caches again: three of 201 MB 130 -> 118 us (5.1 TB/s; 330 -> 305 us with
@@ -688,7 +694,7 @@ hipError_t launch_l1_norms(const float* a, const float* b, const float* c, int64
   else if (c) L1K(false, true);
   else L1K(false, false);
 #undef L1K
-  hipLaunchKernelGGL(l1_finalize_kernel, dim3(1), dim3(1024), 0, s, partials, G, out, pred);
+  hipLaunchKernelGGL(l1_finalize_kernel, dim3(1), dim3(1024), 0, s, partials, G, out, host, pred);
   return hipGetLastError();
 }
 

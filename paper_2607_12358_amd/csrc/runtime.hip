@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <mutex>
 #include <vector>
 
 #include "common.h"
@@ -30,6 +31,44 @@ acid_status check_hip(hipError_t e, const char* what) {
 }
 
 namespace {
+
+// Result slots for the models of this process: one page of pinned host memory
+// (allocated with the first model, kept until the process ends) in slots of a
+// cache line, one per live model.  Freeing per model would wait for the
+// device.  Without a free slot a model's results are copied from the device.
+struct ResultSlots {
+  static constexpr int kSlots = 64, kDoubles = 8;
+  std::mutex mu;
+  bool tried = false;
+  double* page = nullptr;
+  uint64_t used = 0;  // one bit per slot
+};
+ResultSlots& result_slots() {
+  static ResultSlots* r = new ResultSlots();  // outlives every model
+  return *r;
+}
+double* result_slot_take() {
+  ResultSlots& r = result_slots();
+  std::lock_guard<std::mutex> lock(r.mu);
+  if (!r.tried) {
+    r.tried = true;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, ResultSlots::kSlots * ResultSlots::kDoubles * sizeof(double),
+                      hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+      r.page = static_cast<double*>(p);
+    else
+      (void)hipGetLastError();
+  }
+  if (!r.page || ~r.used == 0) return nullptr;
+  const int i = __builtin_ctzll(~r.used);
+  r.used |= (uint64_t)1 << i;
+  return r.page + i * ResultSlots::kDoubles;
+}
+void result_slot_give(double* slot) {
+  ResultSlots& r = result_slots();
+  std::lock_guard<std::mutex> lock(r.mu);
+  r.used &= ~((uint64_t)1 << ((slot - r.page) / ResultSlots::kDoubles));
+}
 
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t a) { return (a + kAlign - 1) / kAlign * kAlign; }
@@ -202,6 +241,11 @@ struct acid_model {
   int probe_blocks = 1;  // DiCache probe depth
   char* wb;  // weight arena
   char* ws;  // workspace
+  // Pinned host doubles that the reductions' last kernel writes a signal to,
+  // for calls that return it (a copy from the device was another kernel per
+  // signal).  Null: none left, the result is copied.
+  double* hres = nullptr;
+  bool hres_pending = false;  // written by launches not yet waited for
   WeightLayout wl;
   WorkLayout kl;
   // timing
@@ -534,13 +578,14 @@ acid_status head_forward(acid_model* m, const float* row, const float* hv, float
 
 // TEMNI into m_cur; if m_prev, the relative-L1 drift is reduced into dres.
 acid_status drift(acid_model* m, const float* row, const float* x, const float* m_prev,
-                  float* m_cur, hipStream_t s) {
+                  float* m_cur, hipStream_t s, double* host = nullptr) {
   const int H = m->H();
   double* part = m->kp<double>(m->kl.partials);
   double* dres = m->kp<double>(m->kl.dres);
   return run(m, ACID_K_DRIFT, s, "drift", [&]() {
+    if (host) m->hres_pending = true;
     hipError_t err = launch_temni_drift(x, m->Lv(), H, row, row + H, m_prev, m_cur, part, s);
-    if (err == hipSuccess && m_prev) err = launch_drift_finalize(part, m->Lv(), dres, s);
+    if (err == hipSuccess && m_prev) err = launch_drift_finalize(part, m->Lv(), dres, s, host);
     return err;
   });
 }
@@ -552,10 +597,17 @@ acid_status l1_norms(acid_model* m, const float* a, const float* b, const float*
   double* dres = m->kp<double>(m->kl.dres);
   const int max_groups = (int)(m->Lv() < 1024 ? m->Lv() : 1024);
   ACID_TRY(run(m, ACID_K_DRIFT, s, "l1 norms", [&]() {
-    return launch_l1_norms(a, b, c, n, part, max_groups, dres, s);
+    m->hres_pending = true;
+    return launch_l1_norms(a, b, c, n, part, max_groups, dres, s, nullptr, m->hres);
   }));
-  ACID_HIP(hipMemcpyAsync(out2, dres, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+  if (!m->hres)
+    ACID_HIP(hipMemcpyAsync(out2, dres, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
   ACID_HIP(hipStreamSynchronize(s));
+  m->hres_pending = false;
+  if (m->hres) {
+    out2[0] = m->hres[0];
+    out2[1] = m->hres[1];
+  }
   return ACID_OK;
 }
 
@@ -869,11 +921,14 @@ acid_status enqueue_easycache_graph_loop(acid_model* m, float* x, const float* s
   return ACID_OK;
 }
 
+// The signal of a drift() that was given m->hres.
 acid_status read_drift(acid_model* m, double* s_out, hipStream_t s) {
-  double res[3];
-  ACID_HIP(hipMemcpyAsync(res, m->kp<double>(m->kl.dres), sizeof res, hipMemcpyDeviceToHost, s));
+  if (!m->hres)
+    ACID_HIP(hipMemcpyAsync(s_out, m->kp<double>(m->kl.dres) + 2, sizeof *s_out,
+                            hipMemcpyDeviceToHost, s));
   ACID_HIP(hipStreamSynchronize(s));
-  *s_out = res[2];
+  m->hres_pending = false;
+  if (m->hres) *s_out = m->hres[0];
   return ACID_OK;
 }
 
@@ -996,6 +1051,7 @@ acid_status acid_model_create(const acid_dit_config* cfg, void* weights_dev, voi
       return set_error(ACID_ERR_SHAPE, "weight layout: concatenated operands are not adjacent");
     }
   }
+  m->hres = result_slot_take();
   *out = m;
   return ACID_OK;
 }
@@ -1066,6 +1122,8 @@ void acid_model_destroy(acid_model* m) {
   for (auto e : m->pool) (void)hipEventDestroy(e);
   if (m->gexec) (void)hipGraphExecDestroy(m->gexec);
   if (m->cap) (void)hipStreamDestroy(m->cap);
+  // A slot that a failed call may still write to is not handed out again.
+  if (m->hres && !m->hres_pending) result_slot_give(m->hres);
   delete m;
 }
 
@@ -1272,7 +1330,7 @@ acid_status acid_drift_signal(acid_model* m, const float* x_dev, float sigma,
   if (!m || !x_dev || !m_cur_dev || !s_out) return set_error(ACID_ERR_INVALID_ARG, "NULL argument");
   float* row = m->kp(m->kl.modtab);
   ACID_TRY(temni_pair(m, sigma, row, stream));
-  ACID_TRY(drift(m, row, x_dev, m_prev_dev, m_cur_dev, stream));
+  ACID_TRY(drift(m, row, x_dev, m_prev_dev, m_cur_dev, stream, m->hres));
   if (!m_prev_dev) {
     ACID_HIP(hipStreamSynchronize(stream));
     *s_out = NAN;
@@ -1308,7 +1366,7 @@ acid_status acid_denoise_loop(acid_model* m, float* x_dev, const float* sigmas_h
     int32_t gate_compute = 1;
     if (mode == ACID_MODE_ACID) {
       const float* mprev = i > 0 ? mbuf[cur ^ 1] : nullptr;
-      ACID_TRY(drift(m, row, x_dev, mprev, mbuf[cur], stream));
+      ACID_TRY(drift(m, row, x_dev, mprev, mbuf[cur], stream, m->hres));
       if (mprev) ACID_TRY(read_drift(m, &s, stream));
       cur ^= 1;
       ACID_TRY(acid_gate(&st, gate, s, &gate_compute, &tau));

@@ -1,0 +1,69 @@
+"""Signals returned to the host through the models' shared page of pinned
+memory: models beyond its 64 slots (which copy from the device instead) give
+the same values, slots of destroyed models are handed out again, and two
+models used from two threads and streams do not see each other's results."""
+import threading
+
+import pytest
+import torch
+
+import acid_inputs as ai
+from gpu_util import need_gpu
+
+pytestmark = pytest.mark.gpu
+
+CFG = ai.TINY.replace(n_steps=2)
+
+
+def _model(P, seed=0):
+    m = P.Model(CFG, max_steps=2)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    for tid, (_, shape) in enumerate(ai.manifest(CFG)):
+        m.load_tensor(tid, torch.randn(shape, generator=g, device="cuda") * 0.02)
+    return m
+
+
+def test_more_models_than_slots_and_reuse():
+    P = need_gpu()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    x, p, c = (torch.randn((CFG.n_video, CFG.hidden), generator=g, device="cuda") for _ in range(3))
+    m_cur = torch.empty_like(x)
+    for _ in range(2):  # the second round takes the slots the first gave back
+        models = [_model(P) for _ in range(70)]
+        sums = {m.l1_norms(x, p, c) for m in models}
+        drifts = {m.drift_signal(x, 0.7, p, m_cur) for m in models}
+        assert len(sums) == 1 and len(drifts) == 1
+        ref = float((x - p).abs().double().sum()), float(c.abs().double().sum())
+        assert next(iter(sums)) == pytest.approx(ref, rel=1e-12)
+        del models
+
+
+def test_two_threads_two_streams():
+    P = need_gpu()
+    models = [_model(P, s) for s in (3, 4)]
+    data, want = [], []
+    for i, m in enumerate(models):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(10 + i)
+        t = [torch.randn((CFG.n_video, CFG.hidden), generator=g, device="cuda") for _ in range(3)]
+        data.append(t)
+        want.append((m.l1_norms(*t), m.drift_signal(t[0], 0.5, t[1], torch.empty_like(t[0]))))
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(i):
+        st = torch.cuda.Stream()
+        x, p, c = data[i]
+        with torch.cuda.stream(st):
+            m_cur = torch.empty_like(x)
+            for _ in range(50):
+                got = (models[i].l1_norms(x, p, c), models[i].drift_signal(x, 0.5, p, m_cur))
+                if got != want[i]:
+                    bad.append((i, got, want[i]))
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    assert not bad, bad[:2]
