@@ -45,6 +45,14 @@ struct AttnLds {
   static constexpr size_t BYTES = (size_t)2 * (K_ELEMS + V_ELEMS) * sizeof(bf16);
 };
 
+// Dynamic LDS of a launch: a ring per key range, reused by the merge of the
+// ranges (each wave's O^T in fp32, and m and l per lane).
+template <int D, int NW, int KS>
+constexpr size_t attn_lds_bytes() {
+  const size_t ring = KS * AttnLds<D>::BYTES, merge = (size_t)NW * 64 * (D / 2 * 4 + 8);
+  return KS > 1 && merge > ring ? merge : ring;
+}
+
 // Keys are staged into the K tile in the order pi(j) = j with bits 2 and 3
 // swapped (an involution).  Then the 8 probabilities a lane feeds to one
 // P V^T MFMA step are 8 consecutive keys, so the matching V^T operand is one
@@ -112,7 +120,13 @@ __device__ __forceinline__ float half_swap_max(float v) {
 // depend on the order of the keys, so the ragged last tile (keys up to L)
 // is processed first, staged through registers and masked in the prologue;
 // every tile of the loop is full and arrives by DMA.
-template <int D, int NW, bool kPre>
+//
+// KS > 1 (short sequences): the workgroup's NW waves form KS groups of QW =
+// NW / KS, each with LDS buffers of its own.  The groups hold the same 32 QW
+// queries and take KS contiguous ranges of the key tiles (the ragged tile
+// belongs to the last), running the pipeline above on them; their O and l
+// meet in LDS and are added in group order, weighted by 2^(m - max m).
+template <int D, int NW, bool kPre, int KS = 1>
 __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* Q,
                                                            const bf16* Kp,
                                                            const bf16* Vt,
@@ -122,23 +136,26 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
                                                            const int32_t* pred) {
   if (pred && *pred == 0) return;  // predicated off by the device gate
   using Ld = AttnLds<D>;
-  constexpr int BQ = 32 * NW, NT = 64 * NW;  // queries / threads per workgroup
+  constexpr int QW = NW / KS;                // waves per key range
+  constexpr int BQ = 32 * QW, NT = 64 * QW;  // queries / threads per key range
   constexpr int KLD = Ld::KLD, VLD = Ld::VLD;
   constexpr int NK = D / 16;     // MFMA K-steps over the head dim
   constexpr int ND = D / 32;     // 32-row blocks of O^T
-  constexpr int CPT = D / (8 * NW);  // 16-byte chunks per thread per tile (K, and V^T)
+  constexpr int CPT = D / (8 * QW);  // 16-byte chunks per thread per tile (K, and V^T)
   constexpr int KCH = D / 8;     // 16-byte chunks per K row
   constexpr int KROWS_PER_KB = 1024 / (2 * D);  // K rows per 1 KB
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16* Ks = reinterpret_cast<bf16*>(smem);
+  const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = KS > 1 ? wave_wg / QW : 0;  // key range
+  bf16* Ks = reinterpret_cast<bf16*>(smem + grp * Ld::BYTES);
   bf16* Vs = Ks + 2 * Ld::K_ELEMS;
 
   const int64_t n_qt = (L + BQ - 1) / BQ;
   const int64_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
   const int head = (int)(item / n_qt);
   const int64_t qt = item - (int64_t)head * n_qt;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x - grp * NT, lane = tid & 63;
+  const int wave = wave_wg - grp * QW;
   const int lr = lane & 31, lg = lane >> 5;
   const int64_t qrow = qt * BQ + wave * 32 + lr;
 
@@ -187,7 +204,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
   // w and w + 4) wave w issues the blocks of both, so wave w + 4 issues no
   // global loads in the loop.  Per-lane byte offsets relative to the tile's
   // first element, and the block each DMA fills:
-  constexpr bool kPairDma = NW == 8;
+  constexpr bool kPairDma = NW == 8 && KS == 1;
   constexpr int NB = kPairDma ? 2 * CPT : CPT;
   const bool dma_wave = !kPairDma || wave < 4;
   uint32_t koff[NB], voff[NB];
@@ -374,8 +391,10 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
 
   // Processing order of the key tiles: the ragged tile (if any) first, then
   // the full tiles in order.  u >= 1 maps to the full tile u - has_tail.
-  const int nkv = (Li + BKV - 1) / BKV;
-  const int has_tail = (Li % BKV) != 0;
+  const int tiles = (Li + BKV - 1) / BKV;
+  const int t0 = KS > 1 ? tiles * grp / KS : 0;  // first tile of this key range
+  const int nkv = KS > 1 ? tiles * (grp + 1) / KS - t0 : tiles;
+  const int has_tail = grp == KS - 1 && (Li % BKV) != 0;
   // One pipeline iteration: sc holds S of processed tile it; S of tile it+1
   // goes to sn (on the last tile this reads a stale buffer and is dropped).
   // One pipeline iteration: sc holds the exp2 arguments of processed tile
@@ -392,8 +411,8 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
   // and forms the probabilities again.
   constexpr bool kOptimistic = D == 64;
   auto iter = [&](f32x16(&sc)[2], f32x16(&sn)[2], int it) {
-    if (it + 2 < nkv) stage_k_dma(it & 1, (it + 2 - has_tail) * BKV);
-    if (it + 1 < nkv) stage_v_dma((it + 1) & 1, (it + 1 - has_tail) * BKV);
+    if (it + 2 < nkv) stage_k_dma(it & 1, (t0 + it + 2 - has_tail) * BKV);
+    if (it + 1 < nkv) stage_v_dma((it + 1) & 1, (t0 + it + 1 - has_tail) * BKV);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (!kOptimistic) {
       m_run = m_nx;
@@ -530,12 +549,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
 
   f32x16 sa[2], sb[2];
   if (has_tail) {
-    stage_tail(0, (nkv - 1) * BKV);
-  } else {
-    stage_k_dma(0, 0);
-    stage_v_dma(0, 0);
+    stage_tail(0, (tiles - 1) * BKV);
+  } else if (KS == 1 || nkv > 0) {
+    stage_k_dma(0, t0 * BKV);
+    stage_v_dma(0, t0 * BKV);
   }
-  if (nkv > 1) stage_k_dma(1, (1 - has_tail) * BKV);
+  if (nkv > 1) stage_k_dma(1, (t0 + 1 - has_tail) * BKV);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if constexpr (kPre) set_cneg(0.0f);
@@ -546,7 +565,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
   if (has_tail) {
     // Keys past L get score -inf.  S^T row kb*32 + 8 (r/4) + 4 lg + r%4
     // holds key j0 + key_perm(row).
-    const int j0 = (nkv - 1) * BKV;
+    const int j0 = (tiles - 1) * BKV;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -555,15 +574,21 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
         if (key >= Li) sa[kb][r] = -__builtin_inff();
       }
   }
-  if constexpr (kPre) {
-    // The first reference is the first tile's row max (held against m = 0).
+  // The first reference is the first tile's row max.  A key range whose first
+  // tile has only scores of -inf starts from 0 instead.
+  auto first_ref = [&]() {
     first_max(sa);
+    if (KS > 1 && m_run == -__builtin_inff()) m_run = 0.f;
+  };
+  if constexpr (kPre) {
+    first_ref();  // held against m = 0
     sub_all(sa, m_run);
     set_cneg(-m_run);
     m_nx = m_run;
-  } else if constexpr (kOptimistic) {
-    first_max(sa);
+  } else if constexpr (kOptimistic || KS > 1) {
+    first_ref();
     shift(sa);
+    m_nx = m_run;
   } else {
     row_max_shift(sa);
   }
@@ -574,6 +599,57 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
   }
   if (it < nkv) iter(sa, sb, it);
 
+  if constexpr (KS > 1) {
+    // The longest range's barriers, one per tile.
+    const int most = (tiles + KS - 1) / KS;
+    for (int i = nkv; i < most; ++i) __builtin_amdgcn_s_barrier();
+    if (nkv == 0) {  // no keys: scores of a stale buffer were formed and dropped
+      m_run = -__builtin_inff();
+      l_run = 0.f;
+    }
+    l_run += __shfl_xor(l_run, 32, 64);
+    __syncthreads();
+    // [wave][block, group of four rows][lane], then (m, l) per wave and lane.
+    constexpr int NCH = ND * 4;
+    static_assert(NW * (NCH * 16 + 8) * 64 <= attn_lds_bytes<D, NW, KS>() && NCH % KS == 0, "");
+    f32x4* po = reinterpret_cast<f32x4*>(smem);
+    float2* pm = reinterpret_cast<float2*>(smem + NW * NCH * 16 * 64);
+#pragma unroll
+    for (int db = 0; db < ND; ++db)
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg)
+        po[(wave_wg * NCH + db * 4 + rg) * 64 + lane] =
+            f32x4{o[db][4 * rg], o[db][4 * rg + 1], o[db][4 * rg + 2], o[db][4 * rg + 3]};
+    pm[wave_wg * 64 + lane] = make_float2(m_run, l_run);
+    __syncthreads();
+    float w[KS], mx = -__builtin_inff(), l = 0.f;
+#pragma unroll
+    for (int g = 0; g < KS; ++g) {
+      w[g] = pm[(g * QW + wave) * 64 + lane].x;
+      mx = fmaxf(mx, w[g]);
+    }
+#pragma unroll
+    for (int g = 0; g < KS; ++g) {
+      w[g] = __builtin_amdgcn_exp2f(w[g] - mx);
+      l += w[g] * pm[(g * QW + wave) * 64 + lane].y;
+    }
+    const float inv = 1.0f / l;
+    if (qrow < L) {
+      bf16* orow = O + qrow * o_ld + (int64_t)head * D;
+#pragma unroll
+      for (int i = 0; i < NCH / KS; ++i) {  // each group stores its share of the row blocks
+        const int c = grp * (NCH / KS) + i;
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int g = 0; g < KS; ++g) a += w[g] * po[((g * QW + wave) * NCH + c) * 64 + lane];
+        bf16x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (bf16)(a[e] * inv);
+        *reinterpret_cast<bf16x4*>(orow + (c >> 2) * 32 + 8 * (c & 3) + 4 * lg) = v;
+      }
+    }
+    return;
+  }
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = 1.0f / l_tot;
   if (qrow < L) {
@@ -747,14 +823,12 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
   }
 }
 
-// Waves per workgroup: 8 for d = 128 (a staged K/V tile feeds 256 queries),
-// 4 for d = 64 (finer grid for the shorter sequences of that configuration).
-template <int D, bool kPre>
-hipError_t launch_bf16(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
-                       int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s,
-                       const int32_t* pred) {
-  constexpr int NW = D == 128 ? 8 : 4;
-  constexpr int BQ = 32 * NW;
+template <int D, int NW, bool kPre, int KS>
+hipError_t launch_bf16_form(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
+                            int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s,
+                            const int32_t* pred) {
+  constexpr int BQ = 32 * NW / KS;
+  constexpr size_t kLds = attn_lds_bytes<D, NW, KS>();
   // The dynamic-LDS attribute is set once per device (one bit each).
   static std::atomic<uint64_t> attr_set{0};
   int dev = 0;
@@ -762,17 +836,43 @@ hipError_t launch_bf16(int n_heads, int64_t L, const void* q, const void* k, con
   if (err != hipSuccess) return err;
   const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
   if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-    err = hipFuncSetAttribute((const void*)attn_bf16_kernel<D, NW, kPre>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)AttnLds<D>::BYTES);
+    err = hipFuncSetAttribute((const void*)attn_bf16_kernel<D, NW, kPre, KS>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (err != hipSuccess) return err;
     attr_set.fetch_or(bit, std::memory_order_release);
   }
   const float scale_log2 = attn_q_scale(D);
   dim3 grid((unsigned)(((L + BQ - 1) / BQ) * n_heads));
-  hipLaunchKernelGGL((attn_bf16_kernel<D, NW, kPre>), grid, dim3(64 * NW), AttnLds<D>::BYTES, s,
+  hipLaunchKernelGGL((attn_bf16_kernel<D, NW, kPre, KS>), grid, dim3(64 * NW), kLds, s,
                      (const bf16*)q, (const bf16*)k, (const bf16*)vt, L, vt_ld, n_heads,
                      (bf16*)o, o_ld, scale_log2, pred);
   return hipGetLastError();
+}
+
+// Waves per workgroup: 8 for d = 128 (a staged K/V tile feeds 256 queries),
+// 4 for d = 64 (finer grid for the shorter sequences of that configuration).
+// Short sequences, whose workgroups would leave CUs idle, split the keys over
+// the waves instead: d = 64 in four (64 queries a workgroup) or two (128), d =
+// 128 in two (128), the most that gives at most one workgroup per CU.  In one
+// round it runs 1.3-1.8 times as fast (12 heads of 128: 1024 tokens 31.5 ->
+// 21.4 us, 1560 44.5 -> 30.3, 2340 60.8 -> 45.1; 16 heads of 64, 1024 tokens:
+// 20.6 -> 12.8); with two rounds it loses (3000 tokens 74.0 -> 98.1 us; 16
+// heads of 64, 4096 tokens 86.8 -> 124.9), since a split workgroup fills its
+// CU's LDS or registers alone and streams K and V for fewer queries.
+template <int D, bool kPre>
+hipError_t launch_bf16(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
+                       int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s,
+                       const int32_t* pred) {
+  const int64_t cus = device_cus();
+  auto one_round = [&](int queries) { return (L + queries - 1) / queries * n_heads <= cus; };
+  if constexpr (D == 64) {
+    if (one_round(64))
+      return launch_bf16_form<64, 8, kPre, 4>(n_heads, L, q, k, vt, vt_ld, o, o_ld, s, pred);
+  }
+  if (one_round(128))
+    return launch_bf16_form<D, 8, kPre, 2>(n_heads, L, q, k, vt, vt_ld, o, o_ld, s, pred);
+  return launch_bf16_form<D, D == 128 ? 8 : 4, kPre, 1>(n_heads, L, q, k, vt, vt_ld, o, o_ld, s,
+                                                        pred);
 }
 
 template <int D>

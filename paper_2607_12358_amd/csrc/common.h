@@ -72,6 +72,9 @@ inline float attn_q_scale(int d) { return 1.4426950408889634f / sqrtf((float)d);
 // ---------------------------------------------------------------- launchers
 // Each returns hipGetLastError() of its launch.
 
+// Compute units of the current device.
+int device_cus();
+
 // Elementwise / row kernels (elementwise.hip)
 // A kernel given a predicate `pred` (a device int32) does nothing when
 // *pred == 0: the device-resident gate's skip decision.

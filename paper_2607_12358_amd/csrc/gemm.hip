@@ -949,21 +949,8 @@ __global__ __launch_bounds__(512, OCC) void gemm_f32_kernel(const float* A, cons
 // 256 KB of partial sums, which the reduction reads back, and with shorter
 // ranges that costs more than the fuller round saves (measured: split into
 // K ranges of 256-1024, the small configuration's GEMMs ran twice as long).
-int cu_count() {
-  static std::atomic<int> cus{0};
-  int c = cus.load(std::memory_order_relaxed);
-  if (c == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        c < 1)
-      c = 256;
-    cus.store(c, std::memory_order_relaxed);
-  }
-  return c;
-}
 int choose_split(int64_t tiles, int K, int64_t& rem) {
-  const int cus = cu_count();
+  const int cus = device_cus();
   rem = tiles % cus;
   if (rem == 0 || 2 * rem > cus) return 1;
   int S = (int)(cus / rem);
@@ -986,7 +973,7 @@ int choose_split(int64_t tiles, int K, int64_t& rem) {
 // time per area is; every tile gives the same bits.
 enum class Tile { k256, k256x128, k128, k64 };
 Tile choose_tile(int64_t M, int N, int64_t tiles, int64_t rem, int split) {
-  const int64_t cus = cu_count();
+  const int64_t cus = device_cus();
   auto rounds = [&](int tm, int tn) {
     return (double)(((M + tm - 1) / tm * (N / tn) + cus - 1) / cus);
   };
@@ -1049,7 +1036,7 @@ hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const 
     // 64 x 64 tiles, or 32 x 32 ones where those leave most CUs idle: a round
     // of 32 x 32 tiles takes a quarter of the time, and about a fifth more
     // for its shorter K ranges per wave and its reduction.
-    const int64_t cus = cu_count();
+    const int64_t cus = device_cus();
     const int64_t t64 = (M + 63) / 64 * (N / 64), t32 = (M + 31) / 32 * (N / 32);
     if ((double)((t32 + cus - 1) / cus) * 0.3 < (double)((t64 + cus - 1) / cus))
       hipLaunchKernelGGL((gemm_f32_kernel<KIND, 32, 32, 1, 1, 4, 2, 4, 4>), ring_grid(t32),
@@ -1062,6 +1049,21 @@ hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const 
 }
 
 }  // namespace
+
+// The device's CUs (256 where it cannot be asked).
+int device_cus() {
+  static std::atomic<int> cus{0};
+  int c = cus.load(std::memory_order_relaxed);
+  if (c == 0) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        c < 1)
+      c = 256;
+    cus.store(c, std::memory_order_relaxed);
+  }
+  return c;
+}
 
 hipError_t launch_linear(int dtype, int64_t M, int N, int K, const void* a, const void* wt,
                          const acid_epilogue_args& ea, hipStream_t s, const int32_t* pred,

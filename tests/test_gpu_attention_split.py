@@ -1,0 +1,76 @@
+"""bf16 attention's key split (short sequences: the waves of a workgroup take
+ranges of the key tiles and merge in LDS) against the definition, at tile
+counts around the number of ranges, ragged and not; and the unsplit kernel at
+the same short lengths, which many heads select."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from gpu_util import BF16_U, assert_elementwise, attention_bound, bf16_values, need_gpu, to_dev, to_np
+from test_gpu_kernels import prescale_q
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(P, nh, L, d, prescaled, std=1.0, check=(0,), grow=False):
+    rng = np.random.default_rng(L * 3 + d + nh)
+    q, k, v = (bf16_values(rng.normal(size=(nh, L, d)).astype(np.float32) * s) for s in (std, std, 1.0))
+    if grow:  # the reference moves within each range, by different amounts
+        k = bf16_values(k * (1.0 + 6.0 * np.arange(L) / L)[None, :, None].astype(np.float32))
+    q_dev = q
+    if prescaled:
+        q_dev, q = prescale_q(P, q, d, torch.bfloat16)
+    ld = (L + 7) // 8 * 8
+    vt = np.full((nh, d, ld), np.nan, np.float32)
+    vt[:, :, :L] = v.transpose(0, 2, 1)
+    args = [to_dev(t, torch.bfloat16) for t in (q_dev, k, vt)]
+    outs = [torch.full((L, nh * d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    for o in outs:
+        P.attention(*args, o, q_prescaled=prescaled)
+    assert torch.equal(outs[0], outs[1]) and bool(torch.isfinite(outs[0]).all())
+    for j in check:
+        ref = O.attention(q[j], k[j], v[j])
+        assert_elementwise(to_np(outs[0][:, j * d:(j + 1) * d]), ref, attention_bound(q[j], k[j], v[j]),
+                           1.05 * BF16_U, f"{nh} heads L={L} d={d} head {j}")
+
+
+@pytest.mark.parametrize("prescaled", [False, True], ids=["plain-q", "prescaled-q"])
+@pytest.mark.parametrize("d", [64, 128])
+# 1 to 9 tiles of 64 keys, with and without a ragged one; 1037: 17 tiles
+@pytest.mark.parametrize("nh", [2, 20])  # d = 64: four ranges, or two (from 833 tokens on)
+@pytest.mark.parametrize("L", [1, 33, 64, 65, 128, 129, 192, 255, 256, 257, 320, 383, 576, 1037, 1408])
+def test_split_over_key_ranges(L, nh, d, prescaled):
+    _case(need_gpu(), nh, L, d, prescaled, check=(0, 1))
+
+
+@pytest.mark.parametrize("prescaled", [False, True], ids=["plain-q", "prescaled-q"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_split_with_growing_scores(d, prescaled):
+    _case(need_gpu(), 2, 700, d, prescaled, std=2.0, check=(0, 1), grow=True)
+
+
+@pytest.mark.parametrize("prescaled", [False, True], ids=["plain-q", "prescaled-q"])
+@pytest.mark.parametrize("d,nh", [(64, 1024), (128, 600)])
+@pytest.mark.parametrize("L", [64, 130, 320])
+def test_unsplit_at_short_lengths(L, d, nh, prescaled):
+    _case(need_gpu(), nh, L, d, prescaled, check=(0, nh // 2, nh - 1))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_split_range_of_masked_keys(d):
+    """Keys masked by a -inf score (an additive mask carried in one channel)
+    over whole key ranges: their ranges get no weight and no NaN."""
+    P = need_gpu()
+    L = 512
+    rng = np.random.default_rng(d)
+    q, k, v = (bf16_values(rng.normal(size=(1, L, d)).astype(np.float32)) for _ in range(3))
+    q[:, :, 0] = 1.0
+    masked = np.zeros(L, bool)
+    masked[: L // 2] = True
+    k[:, masked, 0] = -np.inf
+    o = torch.empty((L, d), dtype=torch.bfloat16, device="cuda")
+    vt = np.ascontiguousarray(v.transpose(0, 2, 1))
+    P.attention(*(to_dev(t, torch.bfloat16) for t in (q, k, vt)), o)
+    ref = O.attention(q[0], k[0][~masked], v[0][~masked])
+    np.testing.assert_allclose(to_np(o), ref, rtol=2e-2, atol=2e-2)
