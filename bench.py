@@ -459,6 +459,11 @@ def main() -> int:
 
     # per-kernel-class rates over the timed region
     work = work_per_class(cfg, n_comp, N)
+    if timing.get("cache", (0.0, 0))[1] == 0 and n_comp < N:
+        # the residual cache runs inside the head's LN-modulate: a computed
+        # step also reads x and writes r there, a skipped one reads x and r
+        # in place of h
+        work["ln_mod"] = ("byte", work["ln_mod"][1] + (4.0 * N + 4.0 * n_comp) * cfg.n_video * cfg.hidden)
     kernels = {}
     for name, (ms, launches) in timing.items():
         if launches == 0:

@@ -92,11 +92,15 @@ int64_t drift_partial_count(int64_t rows);
 // the device can write, or null) receives s too.
 hipError_t launch_drift_finalize(const double* partials, int64_t rows, double* out,
                                  hipStream_t s, double* host = nullptr);
-// With `flag` (a device int32) the operation is STORE if *flag, else APPLY;
-// without it, op, skipped when predicated off.
+// op, skipped when predicated off.
 hipError_t launch_cache(int op, const float* x, float* h, float* r, int64_t n,
-                        hipStream_t s, const int32_t* flag = nullptr,
-                        const int32_t* pred = nullptr);
+                        hipStream_t s, const int32_t* pred = nullptr);
+// The cache operation and LN-modulate of the rows it yields (h, or x + r,
+// which is not written); see cache_ln_modulate_kernel.
+hipError_t launch_cache_ln_modulate(int op, const int32_t* flag, int out_dtype, const float* x,
+                                    const float* h, float* r, int64_t rows, int H,
+                                    const float* shift, const float* scale, void* out,
+                                    hipStream_t s);
 // dst = src (n floats, 16-byte aligned) unless predicated off.
 hipError_t launch_copy(const float* src, float* dst, int64_t n, hipStream_t s,
                        const int32_t* pred);

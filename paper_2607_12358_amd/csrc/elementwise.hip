@@ -43,15 +43,11 @@ __device__ __forceinline__ int chunk_index(int lane, int c, int n4) {
   return idx < n4 ? idx : n4 - 1;
 }
 
-// Loads a row into registers and returns (mean, rstd) of LayerNorm
-// (biased variance, eps 1e-6).  All of the row's loads are issued before
-// the first is used.
+// (mean, rstd) of LayerNorm (biased variance, eps 1e-6) of a row held in
+// registers.
 template <int CPL>
-__device__ __forceinline__ void load_row_stats(const float4* __restrict__ xr, int n4, int lane,
-                                               float4 (&v)[CPL], float& mean, float& rstd,
-                                               int H) {
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) v[c] = xr[chunk_index(lane, c, n4)];
+__device__ __forceinline__ void row_stats(const float4 (&v)[CPL], int n4, int lane, float& mean,
+                                          float& rstd, int H) {
   float s = 0.f;
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
@@ -73,6 +69,38 @@ __device__ __forceinline__ void load_row_stats(const float4* __restrict__ xr, in
   rstd = 1.0f / sqrtf(q / (float)H + 1e-6f);
 }
 
+// Loads a row into registers and returns its LayerNorm statistics.  All of
+// the row's loads are issued before the first is used.
+template <int CPL>
+__device__ __forceinline__ void load_row_stats(const float4* __restrict__ xr, int n4, int lane,
+                                               float4 (&v)[CPL], float& mean, float& rstd,
+                                               int H) {
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) v[c] = xr[chunk_index(lane, c, n4)];
+  row_stats<CPL>(v, n4, lane, mean, rstd, H);
+}
+
+// out = LN(v) (1 + scale) + shift for a row v held in registers.
+template <int CPL, typename OutT>
+__device__ __forceinline__ void modulate_row(const float4 (&v)[CPL], float mean, float rstd,
+                                             const float* __restrict__ shift,
+                                             const float* __restrict__ scale, int n4, int lane,
+                                             OutT* __restrict__ out, int64_t row) {
+  const float4* sh4 = reinterpret_cast<const float4*>(shift);
+  const float4* sc4 = reinterpret_cast<const float4*>(scale);
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) {
+    const int j = chunk_index(lane, c, n4);
+    const float4 sc = sc4[j], sh = sh4[j];
+    float4 y;
+    y.x = (v[c].x - mean) * rstd * (1.f + sc.x) + sh.x;
+    y.y = (v[c].y - mean) * rstd * (1.f + sc.y) + sh.y;
+    y.z = (v[c].z - mean) * rstd * (1.f + sc.z) + sh.z;
+    y.w = (v[c].w - mean) * rstd * (1.f + sc.w) + sh.w;
+    store4(out, row * n4 + j, y);
+  }
+}
+
 template <int CPL, typename OutT>
 __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restrict__ x,
                                                           int64_t rows, int H,
@@ -88,19 +116,49 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
   float4 v[CPL];
   float mean, rstd;
   load_row_stats<CPL>(reinterpret_cast<const float4*>(x + row * H), n4, lane, v, mean, rstd, H);
-  const float4* sh4 = reinterpret_cast<const float4*>(shift);
-  const float4* sc4 = reinterpret_cast<const float4*>(scale);
+  modulate_row<CPL, OutT>(v, mean, rstd, shift, scale, n4, lane, out, row);
+}
+
+// The residual cache and the head's LN-modulate of a step in one pass over
+// the rows: STORE r = h - x and normalise h, APPLY normalise x + r.  The head
+// is the only reader of x + r, so APPLY does not write it, and each row is
+// read once where the cache kernel and LN-modulate moved it three more
+// times (32760 rows of 1536: 152 -> 82 us a skipped step; of 3072: 316 -> 178).  With `flag` (the device
+// gate's decision) the operation is STORE if *flag, else APPLY.
+template <int CPL, typename OutT>
+__global__ __launch_bounds__(256) void cache_ln_modulate_kernel(
+    int op, const int32_t* __restrict__ flag, const float* __restrict__ x,
+    const float* __restrict__ h, float* __restrict__ r, int64_t rows, int H,
+    const float* __restrict__ shift, const float* __restrict__ scale, OutT* __restrict__ out) {
+  const bool store = flag ? *flag != 0 : op == ACID_CACHE_STORE;
+  const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (row >= rows) return;  // whole wave leaves together
+  const int n4 = H >> 2;
+  const float4* x4 = reinterpret_cast<const float4*>(x + row * H);
+  const float4* o4 = reinterpret_cast<const float4*>((store ? h : r) + row * H);
+  float4* r4 = reinterpret_cast<float4*>(r + row * H);
+  float4 v[CPL], xv[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     const int j = chunk_index(lane, c, n4);
-    const float4 sc = sc4[j], sh = sh4[j];
-    float4 y;
-    y.x = (v[c].x - mean) * rstd * (1.f + sc.x) + sh.x;
-    y.y = (v[c].y - mean) * rstd * (1.f + sc.y) + sh.y;
-    y.z = (v[c].z - mean) * rstd * (1.f + sc.z) + sh.z;
-    y.w = (v[c].w - mean) * rstd * (1.f + sc.w) + sh.w;
-    store4(out, row * n4 + j, y);
+    xv[c] = x4[j];
+    v[c] = o4[j];
   }
+  __builtin_amdgcn_sched_barrier(0);  // the row's loads stay ahead of its stores
+  if (store) {
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+      r4[chunk_index(lane, c, n4)] = make_float4(v[c].x - xv[c].x, v[c].y - xv[c].y,
+                                                 v[c].z - xv[c].z, v[c].w - xv[c].w);
+  } else {
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+      v[c] = make_float4(xv[c].x + v[c].x, xv[c].y + v[c].y, xv[c].z + v[c].z, xv[c].w + v[c].w);
+  }
+  float mean, rstd;
+  row_stats<CPL>(v, n4, lane, mean, rstd, H);
+  modulate_row<CPL, OutT>(v, mean, rstd, shift, scale, n4, lane, out, row);
 }
 
 // TEMNI m = LN(x) (1 + scale) + shift, stored; if m_prev is given, the
@@ -299,18 +357,6 @@ __global__ __launch_bounds__(256) void cache_kernel(const float* __restrict__ x,
                                                     const int32_t* __restrict__ pred) {
   if (pred && *pred == 0) return;
   cache_body<OP>(x, h, r, n);
-}
-
-// The operation chosen by the device gate's decision: STORE after a computed
-// step, APPLY on a skipped one.
-__global__ __launch_bounds__(256) void cache_by_flag_kernel(const float* __restrict__ x,
-                                                            float* __restrict__ h,
-                                                            float* __restrict__ r, int64_t n,
-                                                            const int32_t* __restrict__ flag) {
-  if (*flag)
-    cache_body<ACID_CACHE_STORE>(x, h, r, n);
-  else
-    cache_body<ACID_CACHE_APPLY>(x, h, r, n);
 }
 
 // dst = src over n floats (16-byte aligned), unless the device gate's flag
@@ -579,6 +625,25 @@ hipError_t launch_ln_modulate(int out_dtype, const float* x, int64_t rows, int H
   return hipGetLastError();
 }
 
+hipError_t launch_cache_ln_modulate(int op, const int32_t* flag, int out_dtype, const float* x,
+                                    const float* h, float* r, int64_t rows, int H,
+                                    const float* shift, const float* scale, void* out,
+                                    hipStream_t s) {
+  if (rows == 0) return hipSuccess;
+  const int cpl = row_chunks(H);
+  dim3 grid((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock));
+#define CL_BF(C) hipLaunchKernelGGL((cache_ln_modulate_kernel<C, bf16>), grid, dim3(256), 0, s, op, flag, x, h, r, rows, H, shift, scale, (bf16*)out)
+#define CL_F(C) hipLaunchKernelGGL((cache_ln_modulate_kernel<C, float>), grid, dim3(256), 0, s, op, flag, x, h, r, rows, H, shift, scale, (float*)out)
+  if (out_dtype == ACID_BF16) {
+    ACID_ROW_DISPATCH(cpl, CL_BF)
+  } else {
+    ACID_ROW_DISPATCH(cpl, CL_F)
+  }
+#undef CL_BF
+#undef CL_F
+  return hipGetLastError();
+}
+
 hipError_t launch_temni_drift(const float* x, int64_t rows, int H, const float* shift,
                               const float* scale, const float* m_prev, float* m_cur,
                               double* partials, hipStream_t s) {
@@ -611,12 +676,10 @@ static unsigned stream_grid(int64_t n) {
 }
 
 hipError_t launch_cache(int op, const float* x, float* h, float* r, int64_t n, hipStream_t s,
-                        const int32_t* flag, const int32_t* pred) {
+                        const int32_t* pred) {
   if (n == 0) return hipSuccess;
   const unsigned blocks = stream_grid(n);
-  if (flag)
-    hipLaunchKernelGGL(cache_by_flag_kernel, dim3(blocks), dim3(256), 0, s, x, h, r, n, flag);
-  else if (op == ACID_CACHE_STORE)
+  if (op == ACID_CACHE_STORE)
     hipLaunchKernelGGL(cache_kernel<ACID_CACHE_STORE>, dim3((unsigned)blocks), dim3(256), 0, s, x, h, r, n, pred);
   else
     hipLaunchKernelGGL(cache_kernel<ACID_CACHE_APPLY>, dim3((unsigned)blocks), dim3(256), 0, s, x, h, r, n, pred);

@@ -551,15 +551,17 @@ acid_status stack_forward(acid_model* m, const float* row, const float* x, const
   return stack_blocks(m, row, 0, m->cfg.n_blocks, s);
 }
 
-// v = LN-modulated head of h_v; EULER variant updates x in place.
-acid_status head_forward(acid_model* m, const float* row, const float* hv, float* v_out,
-                         float* x_euler, float dsigma, hipStream_t s,
-                         const int32_t* pred = nullptr) {
+const float* head_shift(const acid_model* m, const float* row) {
+  return row + 6 * (int64_t)m->cfg.n_blocks * m->H();
+}
+
+// v = the head's GEMM of the LN-modulated rows in the workspace's act buffer;
+// EULER variant updates x in place.
+acid_status head_gemm(acid_model* m, float* v_out, float* x_euler, float dsigma, hipStream_t s,
+                      const int32_t* pred = nullptr) {
   const acid_dit_config& c = m->cfg;
   const int H = c.hidden;
-  const float* shift = row + 6 * (int64_t)c.n_blocks * H;
-  void* act = m->kp<void>(m->kl.act);
-  ACID_TRY(ln_mod(m, hv, m->Lv(), shift, shift + H, act, s, pred));
+  const void* act = m->kp<void>(m->kl.act);
   acid_epilogue_args e = {};
   e.bias = m->wp(m->wl.head_b);
   if (x_euler) {
@@ -574,6 +576,29 @@ acid_status head_forward(acid_model* m, const float* row, const float* hv, float
   return run(m, ACID_K_GEMM_HEAD, s, "head gemm", [&]() {
     return launch_linear(c.dtype, m->Lv(), H, H, act, m->wp<void>(m->wl.head_w), e, s, pred, m->split_ws());
   });
+}
+
+// v = LN-modulated head of h_v; EULER variant updates x in place.
+acid_status head_forward(acid_model* m, const float* row, const float* hv, float* v_out,
+                         float* x_euler, float dsigma, hipStream_t s,
+                         const int32_t* pred = nullptr) {
+  const float* shift = head_shift(m, row);
+  ACID_TRY(ln_mod(m, hv, m->Lv(), shift, shift + m->H(), m->kp<void>(m->kl.act), s, pred));
+  return head_gemm(m, v_out, x_euler, dsigma, s, pred);
+}
+
+// The same head behind the residual cache of base (x_i, or DiCache's probe
+// rows): STORE r = hv - base and the head of hv, or APPLY and the head of
+// base + r; by the device gate's decision where flag is given.
+acid_status cached_head_forward(acid_model* m, const float* row, int op, const int32_t* flag,
+                                const float* base, const float* hv, float* r, float* v_out,
+                                float* x_euler, float dsigma, hipStream_t s) {
+  const float* shift = head_shift(m, row);
+  ACID_TRY(run(m, ACID_K_LN_MOD, s, "cache + ln_modulate", [&]() {
+    return launch_cache_ln_modulate(op, flag, m->cfg.dtype, base, hv, r, m->Lv(), m->H(), shift,
+                                    shift + m->H(), m->kp<void>(m->kl.act), s);
+  }));
+  return head_gemm(m, v_out, x_euler, dsigma, s);
 }
 
 // TEMNI into m_cur; if m_prev, the relative-L1 drift is reduced into dres.
@@ -718,17 +743,13 @@ acid_status dicache_loop(acid_model* m, float* x, const float* sig, int n, const
     const int compute = forced ? (forced[i] != 0) : gate_compute;
     if (compute) {
       ACID_TRY(stack_blocks(m, row, np, m->cfg.n_blocks, s));
-      ACID_TRY(run(m, ACID_K_CACHE, s, "deep residual store", [&]() {
-        return launch_cache(ACID_CACHE_STORE, p, hv, rdeep, nv, s);  // R = h_out_v - p
-      }));
       have_r = true;
-    } else {
-      if (!have_r) return set_error(ACID_ERR_INVALID_ARG, "skip before any computed step");
-      ACID_TRY(run(m, ACID_K_CACHE, s, "deep residual apply", [&]() {
-        return launch_cache(ACID_CACHE_APPLY, p, hv, rdeep, nv, s);  // h_out_v = p + R
-      }));
+    } else if (!have_r) {
+      return set_error(ACID_ERR_INVALID_ARG, "skip before any computed step");
     }
-    ACID_TRY(head_forward(m, row, hv, nullptr, x, sig[i + 1] - sig[i], s));
+    // R = h_out_v - p, or h_out_v = p + R
+    ACID_TRY(cached_head_forward(m, row, compute ? ACID_CACHE_STORE : ACID_CACHE_APPLY, nullptr, p,
+                                 hv, rdeep, nullptr, x, sig[i + 1] - sig[i], s));
     cur ^= 1;
     if (trace) {
       trace[i].compute = compute;
@@ -773,7 +794,6 @@ acid_status enqueue_device_gate_loop(acid_model* m, float* x, const float* sig, 
                                      const float* text, int mode, const acid_gate_params* gate,
                                      const uint8_t* forced, hipStream_t s) {
   const int H = m->H();
-  const int64_t nv = m->Lv() * H;
   const float* table = m->kp(m->kl.modtab);
   float* mbuf[2] = {m->kp(m->kl.m0), m->kp(m->kl.m1)};
   float* r = m->kp(m->kl.r);
@@ -798,12 +818,11 @@ acid_status enqueue_device_gate_loop(acid_model* m, float* x, const float* sig, 
     }
     ACID_TRY(stack_assemble_pred(m, x, text, pred, s));
     ACID_TRY(stack_blocks(m, row, 0, m->cfg.n_blocks, s, pred));
-    if (mode == ACID_MODE_ACID) {
-      ACID_TRY(run(m, ACID_K_CACHE, s, "cache store/apply", [&]() {
-        return launch_cache(ACID_CACHE_STORE, x, hv, r, nv, s, pred);
-      }));
-    }
-    ACID_TRY(head_forward(m, row, hv, nullptr, x, sig[i + 1] - sig[i], s));
+    const float dsig = sig[i + 1] - sig[i];
+    if (mode == ACID_MODE_ACID)
+      ACID_TRY(cached_head_forward(m, row, ACID_CACHE_STORE, pred, x, hv, r, nullptr, x, dsig, s));
+    else
+      ACID_TRY(head_forward(m, row, hv, nullptr, x, dsig, s));
   }
   return ACID_OK;
 }
@@ -850,10 +869,8 @@ acid_status enqueue_dicache_graph_loop(acid_model* m, float* x, const float* sig
     }));
     const int32_t* pred = &dtr[i].compute;
     ACID_TRY(stack_blocks(m, row, np, m->cfg.n_blocks, s, pred));
-    ACID_TRY(run(m, ACID_K_CACHE, s, "deep residual store/apply", [&]() {
-      return launch_cache(ACID_CACHE_STORE, p, hv, rdeep, nv, s, pred);
-    }));
-    ACID_TRY(head_forward(m, row, hv, nullptr, x, sig[i + 1] - sig[i], s));
+    ACID_TRY(cached_head_forward(m, row, ACID_CACHE_STORE, pred, p, hv, rdeep, nullptr, x,
+                                 sig[i + 1] - sig[i], s));
     cur ^= 1;
   }
   return ACID_OK;
@@ -903,7 +920,7 @@ acid_status enqueue_easycache_graph_loop(acid_model* m, float* x, const float* s
     ACID_TRY(stack_blocks(m, row, 0, m->cfg.n_blocks, s, pred));
     ACID_TRY(head_forward(m, row, hv, v, x, dsig, s, pred));  // v_i; x <- x_{i+1}
     ACID_TRY(run(m, ACID_K_CACHE, s, "offset store", [&]() {
-      return launch_cache(ACID_CACHE_STORE, xprev, v, offset, nv, s, nullptr, pred);  // D = v_i - x_i
+      return launch_cache(ACID_CACHE_STORE, xprev, v, offset, nv, s, pred);  // D = v_i - x_i
     }));
     if (i > 0) {
       ACID_TRY(run(m, ACID_K_DRIFT, s, "rate l1 norms", [&]() {
@@ -1316,11 +1333,9 @@ acid_status acid_dit_step(acid_model* m, const float* x_dev, float sigma, const 
   ACID_TRY(modulation_table(m, &sigma, 1, row, stream));
   ACID_TRY(stack_forward(m, row, x_dev, text_dev, stream));
   float* hv = m->kp(m->kl.h) + m->Lt() * m->H();
-  if (resid_dev) {
-    ACID_TRY(run(m, ACID_K_CACHE, stream, "cache store", [&]() {
-      return launch_cache(ACID_CACHE_STORE, x_dev, hv, resid_dev, m->Lv() * m->H(), stream);
-    }));
-  }
+  if (resid_dev)
+    return cached_head_forward(m, row, ACID_CACHE_STORE, nullptr, x_dev, hv, resid_dev, v_dev,
+                               nullptr, 0.f, stream);
   return head_forward(m, row, hv, v_dev, nullptr, 0.f, stream);
 }
 
@@ -1351,7 +1366,6 @@ acid_status acid_denoise_loop(acid_model* m, float* x_dev, const float* sigmas_h
     return dicache_loop(m, x_dev, sigmas_host, n_steps, text_dev, gate, forced, trace, stream);
 
   const int H = m->H();
-  const int64_t nv = m->Lv() * H;
   float* table = m->kp(m->kl.modtab);
   float* mbuf[2] = {m->kp(m->kl.m0), m->kp(m->kl.m1)};
   float* r = m->kp(m->kl.r);
@@ -1372,20 +1386,13 @@ acid_status acid_denoise_loop(acid_model* m, float* x_dev, const float* sigmas_h
       ACID_TRY(acid_gate(&st, gate, s, &gate_compute, &tau));
     }
     const int compute = forced ? (forced[i] != 0) : gate_compute;
-    if (compute) {
-      ACID_TRY(stack_forward(m, row, x_dev, text_dev, stream));
-      if (mode == ACID_MODE_ACID) {
-        ACID_TRY(run(m, ACID_K_CACHE, stream, "cache store", [&]() {
-          return launch_cache(ACID_CACHE_STORE, x_dev, hv, r, nv, stream);
-        }));
-      }
-    } else {
-      ACID_TRY(run(m, ACID_K_CACHE, stream, "cache apply", [&]() {
-        return launch_cache(ACID_CACHE_APPLY, x_dev, hv, r, nv, stream);
-      }));
-    }
+    if (compute) ACID_TRY(stack_forward(m, row, x_dev, text_dev, stream));
     const float dsig = sigmas_host[i + 1] - sigmas_host[i];
-    ACID_TRY(head_forward(m, row, hv, nullptr, x_dev, dsig, stream));
+    if (mode == ACID_MODE_ACID)
+      ACID_TRY(cached_head_forward(m, row, compute ? ACID_CACHE_STORE : ACID_CACHE_APPLY, nullptr,
+                                   x_dev, hv, r, nullptr, x_dev, dsig, stream));
+    else
+      ACID_TRY(head_forward(m, row, hv, nullptr, x_dev, dsig, stream));
     if (trace) {
       trace[i].compute = compute;
       trace[i].gate_compute = gate_compute;
