@@ -608,7 +608,7 @@ acid_status drift(acid_model* m, const float* row, const float* x, const float* 
   double* part = m->kp<double>(m->kl.partials);
   double* dres = m->kp<double>(m->kl.dres);
   return run(m, ACID_K_DRIFT, s, "drift", [&]() {
-    if (host) m->hres_pending = true;
+    if (host && m_prev) m->hres_pending = true;
     hipError_t err = launch_temni_drift(x, m->Lv(), H, row, row + H, m_prev, m_cur, part, s);
     if (err == hipSuccess && m_prev) err = launch_drift_finalize(part, m->Lv(), dres, s, host);
     return err;
