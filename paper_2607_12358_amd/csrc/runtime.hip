@@ -53,11 +53,16 @@ double* result_slot_take() {
   if (!r.tried) {
     r.tried = true;
     void* p = nullptr;
+    // A model may be created while another thread captures a stream: an
+    // allocation of this thread is no part of that.
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     if (hipHostMalloc(&p, ResultSlots::kSlots * ResultSlots::kDoubles * sizeof(double),
                       hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
       r.page = static_cast<double*>(p);
     else
       (void)hipGetLastError();
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
   if (!r.page || ~r.used == 0) return nullptr;
   const int i = __builtin_ctzll(~r.used);
