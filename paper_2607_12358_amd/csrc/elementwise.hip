@@ -146,15 +146,16 @@ __global__ __launch_bounds__(256) void cache_ln_modulate_kernel(
     v[c] = o4[j];
   }
   __builtin_amdgcn_sched_barrier(0);  // the row's loads stay ahead of its stores
+  float4 rv[CPL];
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) {  // both operations, so that no branch waits for the loads
+    rv[c] = make_float4(v[c].x - xv[c].x, v[c].y - xv[c].y, v[c].z - xv[c].z, v[c].w - xv[c].w);
+    if (!store)
+      v[c] = make_float4(xv[c].x + v[c].x, xv[c].y + v[c].y, xv[c].z + v[c].z, xv[c].w + v[c].w);
+  }
   if (store) {
 #pragma unroll
-    for (int c = 0; c < CPL; ++c)
-      r4[chunk_index(lane, c, n4)] = make_float4(v[c].x - xv[c].x, v[c].y - xv[c].y,
-                                                 v[c].z - xv[c].z, v[c].w - xv[c].w);
-  } else {
-#pragma unroll
-    for (int c = 0; c < CPL; ++c)
-      v[c] = make_float4(xv[c].x + v[c].x, xv[c].y + v[c].y, xv[c].z + v[c].z, xv[c].w + v[c].w);
+    for (int c = 0; c < CPL; ++c) r4[chunk_index(lane, c, n4)] = rv[c];
   }
   float mean, rstd;
   row_stats<CPL>(v, n4, lane, mean, rstd, H);
