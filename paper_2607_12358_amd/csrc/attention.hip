@@ -96,10 +96,11 @@ __device__ __forceinline__ void dma16(uint64_t base, uint32_t off_bytes, uint32_
 // Bijection from dispatch order to (head, query-tile) work items that gives
 // XCD x (workgroups bid = x, x+8, ...) a contiguous, head-major range, so a
 // head's K/V is streamed through as few L2s as possible.
-__device__ __forceinline__ int64_t attn_xcd_remap(int64_t bid, int64_t T) {
-  constexpr int64_t NX = 8;
-  const int64_t x = bid % NX, local = bid / NX;
-  const int64_t q = T / NX, r = T % NX;
+// The number of items is below 2^26 (checked at the entry): 32-bit divisions.
+__device__ __forceinline__ uint32_t attn_xcd_remap(uint32_t bid, uint32_t T) {
+  constexpr uint32_t NX = 8;
+  const uint32_t x = bid % NX, local = bid / NX;
+  const uint32_t q = T / NX, r = T % NX;
   return (x < r) ? x * (q + 1) + local : r * (q + 1) + (x - r) * q + local;
 }
 
@@ -150,10 +151,10 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
   bf16* Ks = reinterpret_cast<bf16*>(smem + grp * Ld::BYTES);
   bf16* Vs = Ks + 2 * Ld::K_ELEMS;
 
-  const int64_t n_qt = (L + BQ - 1) / BQ;
-  const int64_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
+  const uint32_t n_qt = (uint32_t)((L + BQ - 1) / BQ);
+  const uint32_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
   const int head = (int)(item / n_qt);
-  const int64_t qt = item - (int64_t)head * n_qt;
+  const int64_t qt = item - head * n_qt;
   const int tid = threadIdx.x - grp * NT, lane = tid & 63;
   const int wave = wave_wg - grp * QW;
   const int lr = lane & 31, lg = lane >> 5;
@@ -700,10 +701,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
   // [wave][chunk][query] after it.
   __shared__ f32x4 lds[4 * NC * BT];
   __shared__ float ml[2][4][BT];
-  const int64_t n_qt = (L + BT - 1) / BT;
-  const int64_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
+  const uint32_t n_qt = (uint32_t)((L + BT - 1) / BT);
+  const uint32_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
   const int head = (int)(item / n_qt);
-  const int64_t q0 = (item - (int64_t)head * n_qt) * BT;
+  const int64_t q0 = (int64_t)(item - head * n_qt) * BT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lg = lane >> 5;

@@ -161,11 +161,14 @@ struct ColEpi {
 };
 
 // Bijection from dispatch order to tile order giving XCD x (workgroups
-// bid = x, x+8, ...) the contiguous tile range of its share.
-__device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t T) {
-  constexpr int64_t NX = 8;
-  const int64_t x = bid % NX, local = bid / NX;
-  const int64_t q = T / NX, r = T % NX;
+// bid = x, x+8, ...) the contiguous tile range of its share.  Tile numbers
+// are below 2^29 (the entry bounds the 256 x 256 tiles by 2^23) and divided in 32
+// bits: the 64-bit divisions of a tile's coordinates were a chain that every
+// workgroup waited for before its first load.
+__device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t T) {
+  constexpr uint32_t NX = 8;
+  const uint32_t x = bid % NX, local = bid / NX;
+  const uint32_t q = T / NX, r = T % NX;
   return (x < r) ? x * (q + 1) + local : r * (q + 1) + (x - r) * q + local;
 }
 
@@ -174,16 +177,17 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t T) {
 // (streamed once from HBM) and many weight column blocks (re-read by every
 // row block, so they come from the on-package cache): groups of 2 measured
 // 3-6% faster than 8 on the model shapes here (4 and 3 within noise of 2).
-template <int GM = 2>
-__device__ __forceinline__ void tile_coords(int64_t t, int64_t tiles_m, int tiles_n, int64_t& tm,
+template <uint32_t GM = 2>
+__device__ __forceinline__ void tile_coords(uint32_t t, int64_t tiles_m, int tiles_n, int64_t& tm,
                                             int& tn) {
-  const int64_t per_group = (int64_t)GM * tiles_n;
-  const int64_t g = t / per_group;
-  const int64_t first = g * GM;
-  const int64_t gsize = min((int64_t)GM, tiles_m - first);
-  const int64_t w = t - g * per_group;
-  tm = first + w % gsize;
-  tn = (int)(w / gsize);
+  const uint32_t per_group = GM * (uint32_t)tiles_n;
+  const uint32_t g = t / per_group;
+  const uint32_t first = g * GM;
+  const uint32_t gsize = min(GM, (uint32_t)tiles_m - first);
+  const uint32_t w = t - g * per_group;
+  const uint32_t col = w / gsize;
+  tm = first + (w - col * gsize);
+  tn = (int)col;
 }
 
 // ------------------------------------------------------------ bf16 MFMA
@@ -415,12 +419,12 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_bf16_kernel(const bf16* A
   int64_t item = -1;  // K-split work item, or -1 for a whole tile
   int kbeg = 0, klen = K;
   if ((int64_t)blockIdx.x < tiles_main) {
-    tile_coords(xcd_remap(blockIdx.x, tiles_main), tiles_m, tiles_n, tm, tn);
+    tile_coords(xcd_remap(blockIdx.x, (uint32_t)tiles_main), tiles_m, tiles_n, tm, tn);
   } else {
     item = (int64_t)blockIdx.x - tiles_main;
     klen = K / split;
     kbeg = (int)(item % split) * klen;
-    tile_coords(tiles_main + item / split, tiles_m, tiles_n, tm, tn);
+    tile_coords((uint32_t)(tiles_main + item / split), tiles_m, tiles_n, tm, tn);
   }
   const int64_t m0 = tm * BM;
   const int n0 = tn * BN;
@@ -626,7 +630,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_split_reduce_kernel(int64
   const int64_t tiles_m = (M + BM - 1) / BM;
   int64_t tm;
   int tn;
-  tile_coords(tiles_main + blockIdx.x, tiles_m, tiles_n, tm, tn);
+  tile_coords((uint32_t)tiles_main + blockIdx.x, tiles_m, tiles_n, tm, tn);
   const int64_t m0 = tm * BM;
   const int n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -758,9 +762,10 @@ __global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
   const int64_t tiles_m = (M + TM - 1) / TM;
   int64_t tm;
   int tn;
-  const int64_t bid = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  if (bid >= tiles_m * tiles_n) return;
-  tile_coords<4>(xcd_remap(bid, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
+  const uint32_t tiles = (uint32_t)tiles_m * tiles_n;
+  const uint32_t bid = blockIdx.y * gridDim.x + blockIdx.x;
+  if (bid >= tiles) return;
+  tile_coords<4>(xcd_remap(bid, tiles), tiles_m, tiles_n, tm, tn);
   const int64_t m0 = tm * TM;
   const int n0 = tn * TN;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -857,9 +862,10 @@ __global__ __launch_bounds__(512, OCC) void gemm_f32_kernel(const float* A, cons
   const int64_t tiles_m = (M + TM - 1) / TM;
   int64_t tm;
   int tn;
-  const int64_t bid = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  if (bid >= tiles_m * tiles_n) return;
-  tile_coords<4>(xcd_remap(bid, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
+  const uint32_t tiles = (uint32_t)tiles_m * tiles_n;
+  const uint32_t bid = blockIdx.y * gridDim.x + blockIdx.x;
+  if (bid >= tiles) return;
+  tile_coords<4>(xcd_remap(bid, tiles), tiles_m, tiles_n, tm, tn);
   const int64_t m0 = tm * TM;
   const int n0 = tn * TN;
   const int tid = threadIdx.x, lane = tid & 63;
