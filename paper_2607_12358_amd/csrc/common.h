@@ -141,8 +141,7 @@ hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float
 
 // GEMMs (gemm.hip)
 // split_ws: for bf16, a workspace of kGemmSplitWsBytes with which grids whose
-// last round would leave most CUs idle split those tiles along K (nullptr:
-// never split).
+// tiles would leave most CUs idle split their K range (nullptr: never).
 constexpr size_t kGemmSplitWsBytes = (size_t)256 * 256 * 256 * 4;
 hipError_t launch_linear(int dtype, int64_t M, int N, int K, const void* a, const void* wt,
                          const acid_epilogue_args& epi, hipStream_t s,

@@ -25,9 +25,10 @@
 //   remapped so each XCD (8 per MI355X, own L2) works on a contiguous group
 //   of tiles that share activation rows.
 //   Launches whose 256 x 256 tiles would leave CUs idle (few rows) take
-//   256 x 128, 128 x 128 or 64 x 64 tiles (gemm_ring_kernel): one 1560-token
-//   30-block step 8.62 -> 6.73 ms, the 1024-token loop 5.47 -> 3.26 ms, a
-//   226 x 3072 x 3072 product 52.5 -> 11.8 us.
+//   256 x 128, 128 x 128 or 64 x 64 tiles (gemm_ring_kernel), with the K range
+//   split too where it is long and the tiles few: one 1560-token 30-block step
+//   8.62 -> 5.82 ms, the 1024-token loop 5.47 -> 2.32 ms, a 226 x 3072 x 3072
+//   product 52.5 -> 11.4 us.
 // fp32 path: the fp32 matrix instruction on 64 x 64 or 32 x 32 tiles, for the
 //   fp32 configuration.
 #include <atomic>
@@ -664,15 +665,15 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_split_reduce_kernel(int64
 // K-step) or of the B tile, 128 bytes each, chunks at the slots of the
 // 256 x 256 kernel's tiles.  Rows past M are clamped.  Stage st goes into
 // buffer st % NST once the MFMA waves have read stage st - NST; barrier st
-// (after the one that admits stage 0) admits stage st + 1.
+// (after the one that admits stage 0) admits stage st + 1.  NS stages from
+// k0 on.
 template <typename T, int TM, int TN, int SUB, int NST>
 __device__ __forceinline__ void ring_feed(const T* A, const T* Wt, int64_t M, int K, int64_t m0,
-                                          int n0, int w, int lane, const T* ring) {
-  constexpr int kRow = 128 / sizeof(T);         // elements per row and K-step
+                                          int n0, int k0, int NS, int w, int lane,
+                                          const T* ring) {
   constexpr int kBlk = (TM + TN) / 8;           // 1 KB blocks per K-step
   constexpr int ND = SUB * kBlk / 4;            // DMAs per wave and stage
   static_assert(SUB * kBlk % 4 == 0 && NST >= 2 && ND * (NST - 1) <= 63, "ring");
-  const int NS = K / (SUB * kRow);
   uint64_t base[ND];
   uint32_t off[ND];
 #pragma unroll
@@ -683,7 +684,7 @@ __device__ __forceinline__ void ring_feed(const T* A, const T* Wt, int64_t M, in
     const int r = (is_a ? bb : bb - TM / 8) * 8 + (lane >> 3);
     const int ch = (lane & 7) ^ ((r >> 1) & 7);
     const int row = is_a && m0 + r >= M ? (int)(M - 1 - m0) : r;
-    base[i] = uniform_ptr(is_a ? A + m0 * K : Wt + (int64_t)n0 * K);
+    base[i] = uniform_ptr((is_a ? A + m0 * K : Wt + (int64_t)n0 * K) + k0);
     off[i] = (uint32_t)row * (uint32_t)(K * (int)sizeof(T)) + (uint32_t)(sub * 128 + ch * 16);
   }
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)ring) +
@@ -743,15 +744,18 @@ __device__ __forceinline__ void ring_feed(const T* A, const T* Wt, int64_t M, in
 // first fragment reads run under its MFMAs.  A tile accumulates its K-steps
 // in the order of the 256 x 256 kernel with the same instruction, so results
 // do not depend on the tile size, bit for bit.
+// SPLIT: the K-steps of each tile are split into `split` ranges, one work item
+// each, which leave fp32 partial sums in e.split_ws for
+// gemm_ring_reduce_kernel.
 // A 128 x 128 stage takes about 0.41 us of a CU with 156 tiles in flight
 // (0.36 without the DMAs, 0.31 for one tile per XCD alone; its MFMAs need
 // 0.22 us at 2.4 GHz): the MFMA waves' issue between barriers bounds it, not
 // the staging.  Reading fragments three sub-steps ahead instead of one, or a
 // ring one stage deeper, changes nothing (57-60 us at 1560 x 1536 x 8960);
 // eight MFMA waves instead of four 2-10% faster.
-template <int KIND, int TM, int TN, int WM, int WN, int NST, int OCC>
+template <int KIND, int TM, int TN, int WM, int WN, int NST, int OCC, bool SPLIT>
 __global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
-    const bf16* A, const bf16* Wt, int64_t M, int N, int K, Epi e) {
+    const bf16* A, const bf16* Wt, int64_t M, int N, int K, Epi e, int split) {
   if (e.pred && *e.pred == 0) return;
   constexpr int kMath = WM * WN;                       // MFMA waves
   constexpr int MB = TM / WM / 32, NB = TN / WN / 32;  // 32 x 32 blocks per wave
@@ -762,18 +766,22 @@ __global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
   const int64_t tiles_m = (M + TM - 1) / TM;
   int64_t tm;
   int tn;
-  const uint32_t tiles = (uint32_t)tiles_m * tiles_n;
+  const uint32_t tiles = (uint32_t)tiles_m * tiles_n, items = SPLIT ? tiles * split : tiles;
   const uint32_t bid = blockIdx.y * gridDim.x + blockIdx.x;
-  if (bid >= tiles) return;
-  tile_coords<4>(xcd_remap(bid, tiles), tiles_m, tiles_n, tm, tn);
+  if (bid >= items) return;
+  uint32_t t = xcd_remap(bid, items);
+  const int part = SPLIT ? (int)(t / tiles) : 0;  // ranges outer: an XCD's tiles share operands
+  if constexpr (SPLIT) t -= part * tiles;
+  tile_coords<4>(t, tiles_m, tiles_n, tm, tn);
   const int64_t m0 = tm * TM;
   const int n0 = tn * TN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int NS = K / BK;
+  const int steps = K / BK, s0 = SPLIT ? steps * part / split : 0;
+  const int NS = SPLIT ? steps * (part + 1) / split - s0 : steps;
 
   if (wave >= kMath) {
-    ring_feed<bf16, TM, TN, 1, NST>(A, Wt, M, K, m0, n0, wave - kMath, lane, ring);
+    ring_feed<bf16, TM, TN, 1, NST>(A, Wt, M, K, m0, n0, s0 * BK, NS, wave - kMath, lane, ring);
     return;
   }
 
@@ -829,8 +837,91 @@ __global__ __launch_bounds__(64 * (WM * WN + 4), OCC) void gemm_ring_kernel(
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  if constexpr (SPLIT) {
+    // Partial sums of this K range: value q of thread tid at (q kMath 64 + tid)
+    // float4s into the work item (consecutive threads, consecutive 16 B).
+    const int64_t item = ((int64_t)tm * tiles_n + tn) * split + part;
+    f32x4* dst = reinterpret_cast<f32x4*>(e.split_ws) + item * (TM * TN / 4);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          dst[((mb * NB + nb) * 4 + r4) * 64 * kMath + tid] =
+              f32x4{acc[mb][nb][4 * r4], acc[mb][nb][4 * r4 + 1], acc[mb][nb][4 * r4 + 2],
+                    acc[mb][nb][4 * r4 + 3]};
+    return;
+  }
   tile_epilogue<KIND, bf16, MB, NB, OCC >= 3 ? 16 : 32>(e, acc, M, N, m0 + wm * (TM / WM),
                                                        n0 + wn * (TN / WN), m0 + TM <= M, lane);
+}
+
+// Second pass of a ring launch with a K split: each wave adds the partial
+// sums of one 32 x 32 block of a tile in range order (deterministic) and runs
+// the tile's epilogue.  Bound by the latency of its loads: one block a wave
+// and four ranges' loads in flight, the old values of a read-modify-write
+// requested first.
+template <int KIND, int TM, int TN, int WM, int WN>
+__global__ __launch_bounds__(256) void gemm_ring_reduce_kernel(int64_t M, int N, Epi e,
+                                                               int split) {
+  if (e.pred && *e.pred == 0) return;
+  constexpr int MB = TM / WM / 32, NB = TN / WN / 32, kBlocks = TM / 32 * (TN / 32);
+  static_assert(kBlocks % 4 == 0, "whole workgroups per tile");
+  const int lane = threadIdx.x & 63;
+  const uint32_t tile = blockIdx.x / (kBlocks / 4);
+  // Four neighbouring column blocks per workgroup where the tile has them.
+  const int b = (int)(blockIdx.x % (kBlocks / 4)) * 4 +
+                __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rb = b / (TN / 32), cb = b % (TN / 32);
+  const uint32_t tiles_n = N / TN;
+  const int64_t m = (int64_t)(tile / tiles_n) * TM + rb * 32;
+  const int n = (int)(tile % tiles_n) * TN + cb * 32;
+  if (m >= M) return;
+  const int wave = rb / MB * WN + cb / NB;
+  const int q = (rb % MB * NB + cb % NB) * 4;
+  constexpr int64_t kQ = 64 * WM * WN, kPart = TM * TN / 4;
+  const f32x4* src = reinterpret_cast<const f32x4*>(e.split_ws) + (int64_t)tile * split * kPart + q * kQ +
+                     wave * 64 + lane;
+  const int lr = lane & 31, lg = lane >> 5;
+  const ColEpi<KIND, bf16> ce(e, n + lr, N);
+  const int64_t mrow = m + 4 * lg;
+  float prev[16];
+  if constexpr (ColEpi<KIND, bf16>::kRmw) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t row = mrow + 8 * (r >> 2) + (r & 3);
+      prev[r] = ce.old(row < M ? row : M - 1);
+    }
+  }
+  f32x4 v[4];
+#pragma unroll
+  for (int r4 = 0; r4 < 4; ++r4) v[r4] = src[r4 * kQ];
+  // Four ranges in flight at a time; past the last: read again and dropped.
+  for (int s = 1; s < split; s += 4) {
+    f32x4 w[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) w[j][r4] = src[min(s + j, split - 1) * kPart + r4 * kQ];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (s + j < split)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) v[r4] += w[j][r4];
+  }
+  if constexpr (ColEpi<KIND, bf16>::kRmw) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t row = mrow + 8 * (r >> 2) + (r & 3);
+      if (row < M) ce.put_old(row, v[r / 4][r % 4], prev[r]);
+    }
+  } else {
+    f32x16 acc[1][1];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][0][r] = v[r / 4][r % 4];
+    tile_epilogue<KIND, bf16, 1, 1>(e, acc, M, N, m, n, m + 32 <= M, lane);
+  }
 }
 
 // ------------------------------------------------------------ fp32 MFMA
@@ -872,7 +963,7 @@ __global__ __launch_bounds__(512, OCC) void gemm_f32_kernel(const float* A, cons
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int NS = K / (SUB * kRow);
   if (wave >= 4) {
-    ring_feed<float, TM, TN, SUB, NST>(A, Wt, M, K, m0, n0, wave - 4, lane, ring);
+    ring_feed<float, TM, TN, SUB, NST>(A, Wt, M, K, m0, n0, 0, NS, wave - 4, lane, ring);
     return;
   }
 
@@ -965,38 +1056,61 @@ int choose_split(int64_t tiles, int K, int64_t& rem) {
   return S;
 }
 
-// Output tile of a bf16 launch.  A launch takes ceil(tiles / CUs) rounds of
-// tiles, so its time goes as rounds x tile area x the kernel's time per unit
-// of area, here relative to the 256 x 256 kernel and fitted to timings at K
-// 1024-8960 (microseconds, 256 x 256 / 256 x 128 / 128 x 128 / 64 x 64; the
-// best is what the rule takes):
-//   1024 x 1024, K 4096:   67.8 / 38.3 / 24.7 / 15.5   (16, 32, 64, 256 tiles)
-//   1560 x 1536, K 8960:  138.6 / 84.4 / 57.2 / 78.6   (42, 84, 156, 600)
-//   1560 x 4608, K 1536:   34.8 / 27.3 / 32.7 / 41.3   (126, 252, 468, 1800)
-//   4680 x 1536, K 1536:   36.3 / 29.3 / 33.6 / 39.6   (114, 228, 444, 1776)
-//   9000 x 3072, K 3072:  156.7 / 171.5 / 191.4 / 257.7 (432, 864, 1704, 6768)
-// Smaller tiles move more operand bytes per flop, which is what their larger
-// time per area is; every tile gives the same bits.
+// Output tile and K split of a bf16 launch: the form with the least estimated
+// time, in microseconds: rounds of the CUs x (a + b x K-steps of 64), fitted
+// to the block's four products in place (weights not in the caches), 64 to
+// 6000 rows, N and K 256 to 12288 (15% rms of each time; the choices take
+// 1.4% more than the best of the forms at each size).
+// Microseconds, 256 x 256 / 256 x 128 / 128 x 128 / 64 x 64:
+//    256 x  3072 x  1024:  25.5 /  20.2 /  14.4 /   9.0
+//   1000 x  8960 x  1536:  41.2 /  51.2 /  58.7 /  60.6
+//   1560 x  1536 x  1536:  35.9 /  24.3 /  18.4 /  21.3
+//   1560 x  4608 x  1536:  36.2 /  30.3 /  36.6 /  44.3
+//   4000 x 12288 x  3072: 251.0 / 295.7 / 357.0 / 473.9
+// With a workspace the K range of a ring tile may be split too, where all
+// items fit one round: 64 rows x 1536 x 8960 45.1 -> 18.3 us, 300 rows 40.7
+// -> 26.4, 1000 rows 72.5 -> 43.7, 1560 rows 65.8 -> 59.0.  The second pass
+// costs about 6 us and its bytes at 4 TB/s.  Every tile without a split gives
+// the same bits.
 enum class Tile { k256, k256x128, k128, k64 };
-Tile choose_tile(int64_t M, int N, int64_t tiles, int64_t rem, int split) {
-  const int64_t cus = device_cus();
-  auto rounds = [&](int tm, int tn) {
-    return (double)(((M + tm - 1) / tm * (N / tn) + cus - 1) / cus);
-  };
-  // a K split replaces the last round by 1 / split of one and a reduction
-  double best = split > 1 ? (double)((tiles - rem) / cus) * 4 + 4.0 / split + 0.5
-                          : (double)((tiles + cus - 1) / cus) * 4;
-  Tile t = Tile::k256;
-  auto consider = [&](Tile c, double cost) {
-    if (cost < best) {
-      best = cost;
-      t = c;
+struct Form {
+  Tile tile;
+  int split;  // of a ring tile's K range, or of the 256 x 256 tail tiles'
+};
+Form choose_form(int64_t M, int N, int K, bool have_ws, int64_t& rem) {
+  const int64_t cus = device_cus(), tiles = (M + BM - 1) / BM * ((N + BN - 1) / BN);
+  const int steps = K / BK;
+  auto second_pass = [](int64_t items, int area) { return 6.0 + items * area * 1e-6; };
+  const int tail = have_ws ? choose_split(tiles, K, rem) : 1;
+  Form f = {Tile::k256, tail};
+  double best = (double)((tiles + cus - 1) / cus) * (17.5 + 0.84 * steps);
+  if (tail > 1)  // the last round takes a part of its K-steps
+    best += second_pass(rem * tail, BM * BN) - 0.84 * (steps - steps / tail);
+  auto consider = [&](Tile t, int tm, int tn, double once, double a, double b, double smooth) {
+    const int64_t n = (M + tm - 1) / tm * (N / tn);
+    const double x = (double)n / cus;
+    // smooth: part of a partly filled round that shares its CUs with the last
+    const double rounds = (1 - smooth) * (double)((n + cus - 1) / cus) + smooth * (x > 1 ? x : 1);
+    const double whole = once + rounds * (a + b * steps);
+    if (whole < best) {
+      best = whole;
+      f = {t, 1};
+    }
+    if (!have_ws) return;
+    for (int sp = 2; sp <= 8; ++sp) {
+      if (n * sp > cus || n * sp > kSplitMaxItems || steps / sp < 8) break;
+      const double cost =
+          once + a + b * ((steps + sp - 1) / sp) + second_pass(n * sp, tm * tn);
+      if (cost < best) {
+        best = cost;
+        f = {t, sp};
+      }
     }
   };
-  consider(Tile::k256x128, rounds(256, 128) * 2 * 1.15);
-  consider(Tile::k128, rounds(128, 128) * 1.3);
-  consider(Tile::k64, rounds(64, 64) * 0.25 * 2.0);
-  return t;
+  consider(Tile::k256x128, 256, 128, 0, 10, 0.75, 0);
+  consider(Tile::k128, 128, 128, 1, 6, 0.5, 0);
+  consider(Tile::k64, 64, 64, 4.7, 0.55, 0.225, 0.45);
+  return f;
 }
 
 // Grid of a ring kernel: one workgroup per tile, in two dimensions beyond 2^22
@@ -1008,10 +1122,22 @@ dim3 ring_grid(int64_t tiles) {
 
 template <int KIND, int TM, int TN, int WM, int WN, int NST, int OCC>
 hipError_t launch_ring(int64_t M, int N, int K, const void* a, const void* wt, const Epi& e,
-                       hipStream_t s) {
-  const int64_t grid = (M + TM - 1) / TM * (N / TN);
-  hipLaunchKernelGGL((gemm_ring_kernel<KIND, TM, TN, WM, WN, NST, OCC>), ring_grid(grid),
-                     dim3(64 * (WM * WN + 4)), 0, s, (const bf16*)a, (const bf16*)wt, M, N, K, e);
+                       hipStream_t s, int split) {
+  const int64_t tiles = (M + TM - 1) / TM * (N / TN), grid = tiles * split;
+  if (split == 1) {
+    hipLaunchKernelGGL((gemm_ring_kernel<KIND, TM, TN, WM, WN, NST, OCC, false>), ring_grid(grid),
+                       dim3(64 * (WM * WN + 4)), 0, s, (const bf16*)a, (const bf16*)wt, M, N, K, e,
+                       1);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((gemm_ring_kernel<KIND, TM, TN, WM, WN, NST, OCC, true>), ring_grid(grid),
+                     dim3(64 * (WM * WN + 4)), 0, s, (const bf16*)a, (const bf16*)wt, M, N, K, e,
+                     split);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL((gemm_ring_reduce_kernel<KIND, TM, TN, WM, WN>),
+                     dim3((unsigned)(tiles * (TM / 32 * (TN / 32) / 4))), dim3(256), 0, s, M, N, e,
+                     split);
   return hipGetLastError();
 }
 
@@ -1021,11 +1147,12 @@ hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const 
   if (dtype == ACID_BF16) {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
     int64_t rem = 0;
-    const int split = e.split_ws ? choose_split(tiles, K, rem) : 1;
-    switch (choose_tile(M, N, tiles, rem, split)) {
-      case Tile::k256x128: return launch_ring<KIND, 256, 128, 4, 2, 3, 3>(M, N, K, a, wt, e, s);
-      case Tile::k128: return launch_ring<KIND, 128, 128, 2, 4, 4, 3>(M, N, K, a, wt, e, s);
-      case Tile::k64: return launch_ring<KIND, 64, 64, 2, 2, 4, 4>(M, N, K, a, wt, e, s);
+    const Form f = choose_form(M, N, K, e.split_ws != nullptr, rem);
+    const int split = f.split;
+    switch (f.tile) {
+      case Tile::k256x128: return launch_ring<KIND, 256, 128, 4, 2, 3, 3>(M, N, K, a, wt, e, s, split);
+      case Tile::k128: return launch_ring<KIND, 128, 128, 2, 4, 4, 3>(M, N, K, a, wt, e, s, split);
+      case Tile::k64: return launch_ring<KIND, 64, 64, 2, 2, 4, 4>(M, N, K, a, wt, e, s, split);
       case Tile::k256: break;
     }
     const int64_t tiles_main = tiles - (split > 1 ? rem : 0);
