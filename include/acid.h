@@ -18,8 +18,9 @@
  *     blocks whose sizes the library reports.  An acid_model only borrows
  *     them until acid_model_destroy.
  *   - Every kernel is launched on the stream passed in.  Calls that return a
- *     host value computed on the device (acid_drift_signal, acid_denoise_loop)
- *     synchronise that stream before returning.
+ *     host value computed on the device (acid_drift_signal, acid_l1_norms)
+ *     synchronise that stream before returning; acid_denoise_loop waits for
+ *     each signal that it decides by, and its last step may still run.
  *   - Calls return acid_status and never abort.  acid_last_error() gives a
  *     thread-local message for the last non-OK status.  A HIP error is
  *     returned as ACID_ERR_HIP with the HIP error string in the message.
@@ -313,12 +314,12 @@ acid_status acid_easycache_reuse(float* x_dev, float* x_prev_dev, float* v_dev,
  * gate may be NULL in NOCACHE mode.  forced_schedule_host (NULL or n_steps
  * bytes, 0/1) overrides the executed decision while the gate keeps its own
  * state; its step 0 must be 1.  trace_host (NULL or n_steps entries)
- * receives the per-step trace.  One stream synchronisation per ACID step.
+ * receives the per-step trace.  One wait for the device per ACID step.
  * EASYCACHE mode: per step i >= 1 the L1 sums |x_i - x_{i-1}|, |v_{i-1}| give
  * s_i (NaN until a rate k exists), then the gate; compute -> f_theta, x
  * update by the head's Euler epilogue, D = v_i - x_i and (i >= 1) the new
  * k; skip -> acid_easycache_reuse.  The TEMNI buffers of the workspace hold
- * x_{i-1} and v_{i-1}.  Two stream synchronisations per computed step. */
+ * x_{i-1} and v_{i-1}.  Two waits for the device per computed step. */
 acid_status acid_denoise_loop(acid_model* m, float* x_dev,
                               const float* sigmas_host, int32_t n_steps,
                               const float* text_dev, int32_t mode,

@@ -257,6 +257,11 @@ __global__ __launch_bounds__(256) void temni_drift_kernel(
   }
 }
 
+// One 8-byte store that the host may be watching for.
+__device__ __forceinline__ void store_host(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Sums of u and v over a block of 1024 threads, in thread 0: a fixed
 // butterfly within each wave, then over the 16 waves' sums (two barriers; a
 // binary tree in LDS took ten and 2-3 us more).
@@ -319,7 +324,7 @@ __global__ __launch_bounds__(1024) void drift_finalize_kernel(const double* __re
     out[0] = n;
     out[1] = d;
     out[2] = s;
-    if (host) host[0] = s;
+    if (host) store_host(host, s);
   }
 }
 
@@ -526,8 +531,8 @@ __global__ __launch_bounds__(1024) void l1_finalize_kernel(const double* __restr
     out[0] = u;
     out[1] = w;
     if (host) {
-      host[0] = u;
-      host[1] = w;
+      store_host(host, u);
+      store_host(host + 1, w);
     }
   }
 }

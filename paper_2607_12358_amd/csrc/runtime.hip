@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <chrono>
 #include <mutex>
 #include <vector>
 
@@ -620,20 +621,53 @@ acid_status drift(acid_model* m, const float* row, const float* x, const float* 
   });
 }
 
+// A loop's wait for the n values that a launch writes to the result slot.
+// signal_arm, before the launch, marks them unwritten with a NaN that no
+// kernel produces (a NaN carried over from fp32 ends in zero bits); signal_poll
+// watches them for up to half a millisecond, the length of a step of a short
+// loop, whose host would otherwise wait for the stream's completion signal as
+// well (1024-token loop 2462 -> 2258 us, 128-token fp32 loop 371 -> 315).  Not
+// for calls that return with the stream synchronised, nor while an earlier
+// launch may still write the slot.
+constexpr uint64_t kUnwritten = 0x7ff8a5a55a5a1234ull;
+bool signal_arm(acid_model* m, int n) {
+  if (!m->hres || m->hres_pending) return false;
+  for (int i = 0; i < n; ++i)
+    __atomic_store_n(reinterpret_cast<uint64_t*>(m->hres) + i, kUnwritten, __ATOMIC_RELEASE);
+  return true;
+}
+bool signal_poll(acid_model* m, int n) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 0, spins = 0; i < n;) {
+    if (__atomic_load_n(reinterpret_cast<uint64_t*>(m->hres) + i, __ATOMIC_ACQUIRE) != kUnwritten)
+      ++i;
+    else if (++spins % 64 == 0 &&
+             std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(500))
+      return false;
+  }
+  m->hres_pending = false;
+  return true;
+}
+
 // sum |a - b| (or |a|) and sum |c| (or 0) over n elements into out2 (host).
+// in_loop: returns when the sums are known, which may be before the stream is
+// done.
 acid_status l1_norms(acid_model* m, const float* a, const float* b, const float* c, int64_t n,
-                     double* out2, hipStream_t s) {
+                     double* out2, hipStream_t s, bool in_loop = false) {
   double* part = m->kp<double>(m->kl.partials);
   double* dres = m->kp<double>(m->kl.dres);
   const int max_groups = (int)(m->Lv() < 1024 ? m->Lv() : 1024);
+  const bool armed = in_loop && signal_arm(m, 2);
   ACID_TRY(run(m, ACID_K_DRIFT, s, "l1 norms", [&]() {
     m->hres_pending = true;
     return launch_l1_norms(a, b, c, n, part, max_groups, dres, s, nullptr, m->hres);
   }));
-  if (!m->hres)
-    ACID_HIP(hipMemcpyAsync(out2, dres, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-  ACID_HIP(hipStreamSynchronize(s));
-  m->hres_pending = false;
+  if (!(armed && signal_poll(m, 2))) {
+    if (!m->hres)
+      ACID_HIP(hipMemcpyAsync(out2, dres, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+    ACID_HIP(hipStreamSynchronize(s));
+    m->hres_pending = false;
+  }
   if (m->hres) {
     out2[0] = m->hres[0];
     out2[1] = m->hres[1];
@@ -669,7 +703,7 @@ acid_status easycache_loop(acid_model* m, float* x, const float* sig, int n, con
     double si = NAN, tau = NAN, dx = NAN;
     if (i > 0) {
       double sums[2];
-      ACID_TRY(l1_norms(m, x, xprev, vbuf[cur ^ 1], nv, sums, s));
+      ACID_TRY(l1_norms(m, x, xprev, vbuf[cur ^ 1], nv, sums, s, true));
       dx = sums[0];
       if (have_k) si = k * ratio_or_inf(sums[0], sums[1]);
     }
@@ -690,7 +724,7 @@ acid_status easycache_loop(acid_model* m, float* x, const float* sig, int n, con
       have_offset = true;
       if (i > 0) {
         double sums[2];
-        ACID_TRY(l1_norms(m, v, vbuf[cur ^ 1], nullptr, nv, sums, s));
+        ACID_TRY(l1_norms(m, v, vbuf[cur ^ 1], nullptr, nv, sums, s, true));
         k = ratio_or_inf(sums[0], dx);
         have_k = true;
       }
@@ -740,7 +774,7 @@ acid_status dicache_loop(acid_model* m, float* x, const float* sig, int n, const
     double si = NAN, tau = NAN;
     if (i > 0) {
       double sums[2];
-      ACID_TRY(l1_norms(m, p, pbuf[cur ^ 1], pbuf[cur ^ 1], nv, sums, s));
+      ACID_TRY(l1_norms(m, p, pbuf[cur ^ 1], pbuf[cur ^ 1], nv, sums, s, true));
       si = ratio_or_inf(sums[0], sums[1]);
     }
     int32_t gate_compute = 1;
@@ -944,7 +978,11 @@ acid_status enqueue_easycache_graph_loop(acid_model* m, float* x, const float* s
 }
 
 // The signal of a drift() that was given m->hres.
-acid_status read_drift(acid_model* m, double* s_out, hipStream_t s) {
+acid_status read_drift(acid_model* m, double* s_out, hipStream_t s, bool armed = false) {
+  if (armed && signal_poll(m, 1)) {
+    *s_out = m->hres[0];
+    return ACID_OK;
+  }
   if (!m->hres)
     ACID_HIP(hipMemcpyAsync(s_out, m->kp<double>(m->kl.dres) + 2, sizeof *s_out,
                             hipMemcpyDeviceToHost, s));
@@ -1385,8 +1423,9 @@ acid_status acid_denoise_loop(acid_model* m, float* x_dev, const float* sigmas_h
     int32_t gate_compute = 1;
     if (mode == ACID_MODE_ACID) {
       const float* mprev = i > 0 ? mbuf[cur ^ 1] : nullptr;
+      const bool armed = mprev && signal_arm(m, 1);
       ACID_TRY(drift(m, row, x_dev, mprev, mbuf[cur], stream, m->hres));
-      if (mprev) ACID_TRY(read_drift(m, &s, stream));
+      if (mprev) ACID_TRY(read_drift(m, &s, stream, armed));
       cur ^= 1;
       ACID_TRY(acid_gate(&st, gate, s, &gate_compute, &tau));
     }

@@ -67,3 +67,27 @@ def test_two_threads_two_streams():
     [t.start() for t in ts]
     [t.join() for t in ts]
     assert not bad, bad[:2]
+
+
+@pytest.mark.parametrize("mode", ["acid", "easycache", "dicache"])
+def test_loop_signals_of_nan_latents(mode):
+    """A loop watches for its signals in the pinned slot: NaN signals arrive
+    like any other, and the models of the 65th slot on, which copy theirs, and
+    a repeated loop give the same trace."""
+    P = need_gpu()
+    models = [_model(P) for _ in range(65)]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    x0 = torch.randn((CFG.n_video, CFG.hidden), generator=g, device="cuda")
+    for bad in (False, True):
+        if bad:
+            x0[3, 5] = float("nan")
+        got = []
+        for m in (models[0], models[0], models[64]):
+            x = x0.clone()
+            tr = m.denoise_loop(x, ai.sigmas(2), mode=mode, tau_low=0.05, tau_high=0.2, delta=0.01)
+            got.append((tr.tobytes(), x.cpu().numpy().tobytes()))
+            assert bool(x.isnan().any()) == bad
+            if mode != "easycache":  # its first signal needs two computed steps
+                assert bool(tr["s"][1] != tr["s"][1]) == bad
+        assert got[0] == got[1] == got[2]
