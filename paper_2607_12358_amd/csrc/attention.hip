@@ -680,12 +680,15 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
 // the probabilities in accumulator layout are the B operand of
 // O^T = V^T P^T, and the matching V^T operand is one 16-byte load per four
 // MFMAs.  K and V^T come straight from global memory (16 bytes per lane and
-// four MFMAs of 64 cycles), V of a tile ahead of its score MFMAs, K of the
-// next tile ahead of the softmax; Q is read from LDS.  Bound by the matrix
-// unit (4 L^2 d flops a head at 157 TFLOP/s).  The one-query-per-wave kernel
+// four MFMAs of 64 cycles), V of a tile ahead of its scores and its softmax, K
+// of the next tile under P V and the first scores; Q is read from LDS.
+// Scores are added from sums of 32 products and O from sums of a tile (one
+// chain of all of them was up to 1.8 times as far from 64 bits: 3.3e-7 -> 1.8e-7
+// at 40 keys of 128, 4.1e-7 -> 2.4e-7 at 900 of 64).  Bound by the matrix unit
+// (4 L^2 d flops a head at 157 TFLOP/s).  The one-query-per-wave kernel
 // before it took 2239 us at 16 heads x 1013 x 64 (V^T read four bytes a lane
 // from 64 rows), and a 1013-token fp32 block of that width 2824 us; the block
-// takes 609 us with this kernel.
+// took 609 us with this kernel and takes 282 us with the fp32 GEMM's.
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restrict__ Q,
                                                           const float* __restrict__ Kp,
@@ -725,36 +728,47 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
   float m_run = -__builtin_inff(), l_run = 0.f;
   const int64_t nt = (L + BT - 1) / BT;
   f32x4 kf[NC / 2];
-  auto load_k = [&](int64_t t) {
+  auto load_k = [&](int64_t t, int j0, int j1) {
     const int64_t key = t * BT + lr;
     const float* kr = Kh + (key < L ? key : L - 1) * D + 4 * lg;
 #pragma unroll
-    for (int j = 0; j < NC / 2; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kr + 8 * j);
+    for (int j = j0; j < j1; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kr + 8 * j);
   };
-  if (wave < nt) load_k(wave);
+  if (wave < nt) load_k(wave, 0, NC / 2);
   for (int64_t t = wave; t < nt; t += 4) {
+    // V in two halves, the second once the scores have left K's registers; half
+    // of the next K once the first is used, the rest after P V.
     f32x4 vf[ND][4];
+    auto load_v = [&](int db0, int db1) {
 #pragma unroll
-    for (int db = 0; db < ND; ++db)
+      for (int db = db0; db < db1; ++db)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int64_t key0 = t * BT + 8 * g + 4 * lg;
-        vf[db][g] = *reinterpret_cast<const f32x4*>(Vh + (int64_t)(db * 32 + lr) * vt_ld +
-                                                 (key0 < L ? key0 : 0));
-      }
+        for (int g = 0; g < 4; ++g) {
+          const int64_t key0 = t * BT + 8 * g + 4 * lg;
+          vf[db][g] = *reinterpret_cast<const f32x4*>(Vh + (int64_t)(db * 32 + lr) * vt_ld +
+                                                   (key0 < L ? key0 : 0));
+        }
+    };
+    load_v(0, ND / 2);
     __builtin_amdgcn_sched_barrier(0);
-    f32x16 s;
+    // Sums of 32 products, added up: a chain of all d would round d times.
+    const f32x16 zero = {};
+    f32x16 s = zero;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+    for (int j0 = 0; j0 < NC / 2; j0 += 4) {
+      if (D == 128 && j0) __builtin_amdgcn_sched_barrier(0);  // few reads of Q held ahead
+      f32x16 part = zero;
 #pragma unroll
-    for (int j = 0; j < NC / 2; ++j) {
-      const f32x4 qf = lds[(2 * j + lg) * BT + lr];
+      for (int j = j0; j < j0 + 4; ++j) {
+        const f32x4 qf = lds[(2 * j + lg) * BT + lr];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][i], qf[i], s, 0, 0, 0);
+        for (int i = 0; i < 4; ++i)
+          part = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][i], qf[i], part, 0, 0, 0);
+      }
+      s += part;
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (t + 4 < nt) load_k(t + 4);
+    load_v(ND / 2, ND);
     __builtin_amdgcn_sched_barrier(0);
     if (t * BT + BT > L) {  // the ragged last tile: keys past L, V^T's padding
 #pragma unroll
@@ -788,10 +802,20 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
       l_run += s[r];
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
+    for (int db = 0; db < ND; ++db) {  // a tile's sum, then added to the others'
+      if (db == ND / 2) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 4 < nt) load_k(t + 4, 0, NC / 4);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      f32x16 part = zero;
 #pragma unroll
-      for (int db = 0; db < ND; ++db)
-        o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db][r >> 2][r & 3], s[r], o[db], 0, 0, 0);
+      for (int r = 0; r < 16; ++r)
+        part = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db][r >> 2][r & 3], s[r], part, 0, 0, 0);
+      o[db] += part;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 4 < nt) load_k(t + 4, NC / 4, NC / 2);
   }
   l_run += __shfl_xor(l_run, 32, 64);
   __syncthreads();  // every wave is done with Q
