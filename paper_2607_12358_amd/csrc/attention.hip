@@ -104,6 +104,11 @@ __device__ __forceinline__ uint32_t attn_xcd_remap(uint32_t bid, uint32_t T) {
   return (x < r) ? x * (q + 1) + local : r * (q + 1) + (x - r) * q + local;
 }
 
+// A first softmax reference below this (exp2 domain) is looked at again: a score
+// added to one of this size is rounded by 2^-14 at most, a 32nd of a
+// probability's rounding to bf16.
+constexpr float kLowRef = -1024.f;
+
 // Maximum of a value over the two half-waves (lanes l and l ^ 32).
 __device__ __forceinline__ float half_swap_max(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false,
@@ -396,8 +401,6 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
   const int t0 = KS > 1 ? tiles * grp / KS : 0;  // first tile of this key range
   const int nkv = KS > 1 ? tiles * (grp + 1) / KS - t0 : tiles;
   const int has_tail = grp == KS - 1 && (Li % BKV) != 0;
-  // One pipeline iteration: sc holds S of processed tile it; S of tile it+1
-  // goes to sn (on the last tile this reads a stale buffer and is dropped).
   // One pipeline iteration: sc holds the exp2 arguments of processed tile
   // it (against the reference m); S of tile it+1 goes to sn (on the last
   // tile this reads a stale buffer and is dropped).
@@ -575,24 +578,49 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
         if (key >= Li) sa[kb][r] = -__builtin_inff();
       }
   }
-  // The first reference is the first tile's row max.  A key range whose first
-  // tile has only scores of -inf starts from 0 instead.
+  // The first reference is the first tile's row max, unless that lies so far
+  // below 0 (masked keys: scores of -inf or of the type's lowest values) that
+  // scores added to it would lose their digits, or that it is no score at all.
+  // Then it is the true maximum over this range's keys, from a pass of its own
+  // over K in global memory: no such tile may stand for the range.
+  bool no_key = false;  // no score of this range can count beside another range's
   auto first_ref = [&]() {
     first_max(sa);
-    if (KS > 1 && m_run == -__builtin_inff()) m_run = 0.f;
+    if (__any(m_run < kLowRef)) {
+      float mx = -__builtin_inff();
+#pragma unroll 1
+      for (int b = 0; b < 2 * nkv; ++b) {
+        const int key = min(t0 * BKV + b * 32 + lr, Li - 1);  // past the end: the last key again
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+          const bf16x8 kf =
+              *reinterpret_cast<const bf16x8*>(Kh + (uint32_t)(key * D + (2 * kk + lg) * 8));
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], s, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+      }
+      mx = half_swap_max(mx);
+      if (m_run < kLowRef) m_run = kPre ? mx : mx * scale_log2;
+      // Plain Q: against a reference of 2^30 and more the shift's multiply-add
+      // leaves the rounding of m itself, beyond what exp2 can hold.
+      if (KS > 1 && (m_run == -__builtin_inff() || (!kPre && m_run < -0x1p30f))) {
+        no_key = true;
+        m_run = 0.f;
+      }
+    }
   };
-  if constexpr (kPre) {
-    first_ref();  // held against m = 0
+  first_ref();
+  if constexpr (kPre) {  // sa was formed with m = 0
     sub_all(sa, m_run);
     set_cneg(-m_run);
-    m_nx = m_run;
-  } else if constexpr (kOptimistic || KS > 1) {
-    first_ref();
-    shift(sa);
-    m_nx = m_run;
   } else {
-    row_max_shift(sa);
+    shift(sa);
   }
+  m_nx = m_run;
   int it = 0;
   for (; it + 1 < nkv; it += 2) {
     iter(sa, sb, it);
@@ -604,10 +632,8 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
     // The longest range's barriers, one per tile.
     const int most = (tiles + KS - 1) / KS;
     for (int i = nkv; i < most; ++i) __builtin_amdgcn_s_barrier();
-    if (nkv == 0) {  // no keys: scores of a stale buffer were formed and dropped
-      m_run = -__builtin_inff();
-      l_run = 0.f;
-    }
+    if (nkv == 0) l_run = 0.f;  // scores of a stale buffer were formed and dropped
+    if (nkv == 0 || no_key) m_run = -__builtin_inff();  // weight 0
     l_run += __shfl_xor(l_run, 32, 64);
     __syncthreads();
     // [wave][block, group of four rows][lane], then (m, l) per wave and lane.

@@ -74,3 +74,71 @@ def test_split_range_of_masked_keys(d):
     P.attention(*(to_dev(t, torch.bfloat16) for t in (q, k, vt)), o)
     ref = O.attention(q[0], k[0][~masked], v[0][~masked])
     np.testing.assert_allclose(to_np(o), ref, rtol=2e-2, atol=2e-2)
+
+
+def _masked_case(P, nh, L, d, prescaled, masked, value, far, check=(0,)):
+    """Keys masked by the score `value` in one channel, all other scores near
+    0 or, with far, near `far`: the oracle over the unmasked keys alone."""
+    rng = np.random.default_rng(L + d + int(np.flatnonzero(masked)[0]))
+    q, k, v = (bf16_values(rng.normal(size=(nh, L, d)).astype(np.float32)) for _ in range(3))
+    q[:, :, :2] = 1.0
+    k[:, :, 0] = np.where(masked, np.float32(value), np.float32(0.0))
+    k[:, :, 1] = far
+    k = bf16_values(k)
+    q_dev = q
+    if prescaled:
+        q_dev, q = prescale_q(P, q, d, torch.bfloat16)
+    vt = np.full((nh, d, (L + 7) // 8 * 8), np.nan, np.float32)
+    vt[:, :, :L] = v.transpose(0, 2, 1)
+    o = torch.empty((L, nh * d), dtype=torch.bfloat16, device="cuda")
+    P.attention(*(to_dev(t, torch.bfloat16) for t in (q_dev, k, vt)), o, q_prescaled=prescaled)
+    # A score is d additions in fp32 of products of size |far|, each rounded by
+    # half a unit there; a weight and the row sum follow it.
+    u = 2.0 ** -24 * abs(far) if far else 0.0
+    slack = 2 * d * u / np.sqrt(d)
+    for j in check:
+        qj, kj, vj = q[j], k[j][~masked], v[j][~masked]
+        bound = attention_bound(qj, kj, vj) + slack * O.attention(qj, kj, np.abs(vj))
+        assert_elementwise(to_np(o[:, j * d:(j + 1) * d]), O.attention(qj, kj, vj), bound,
+                           1.05 * BF16_U, f"{nh} heads L={L} d={d} masked from "
+                           f"{int(np.flatnonzero(masked)[0])} {value} far {far} head {j}")
+
+
+@pytest.mark.parametrize("prescaled", [False, True], ids=["plain-q", "prescaled-q"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("value", [-np.inf, -1e30, -1e6])
+@pytest.mark.parametrize("far", [0.0, -16384.0])
+def test_masked_tile_is_no_reference(value, far, d, prescaled):
+    """A masked tile of 64 keys, at the start of each key range and between
+    (512 keys: ranges of two tiles at d = 64, of four at d = 128), a masked
+    range, a masked ragged tile (processed first), and the unsplit kernel."""
+    P = need_gpu()
+    L = 512
+    for t in range(8):
+        at = np.zeros(L, bool)
+        at[64 * t:64 * t + 64] = True
+        _masked_case(P, 2, L, d, prescaled, at, value, far)
+    for a, b in ((0, 256), (256, 512), (384, 512), (0, 500)):
+        at = np.zeros(L, bool)
+        at[a:b] = True
+        _masked_case(P, 2, L, d, prescaled, at, value, far)
+    at = np.zeros(500, bool)
+    at[448:] = True
+    _masked_case(P, 2, 500, d, prescaled, at, value, far)
+    for n, a in ((150, 128), (192, 0), (192, 64)):  # 300 heads: more workgroups than CUs, no split
+        at = np.zeros(n, bool)
+        at[a:a + 64] = True
+        _masked_case(P, 300, n, d, prescaled, at, value, far, check=(0, 299))
+
+
+@pytest.mark.parametrize("prescaled", [False, True], ids=["plain-q", "prescaled-q"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_no_key_left_is_nan(d, prescaled):
+    """Rows whose scores are all -inf have no softmax: NaN, as 0 / 0."""
+    P = need_gpu()
+    q = torch.ones((2, 130, d), device="cuda", dtype=torch.bfloat16)
+    k = torch.full((2, 130, d), -float("inf"), device="cuda", dtype=torch.bfloat16)
+    vt = torch.ones((2, d, 136), device="cuda", dtype=torch.bfloat16)
+    o = torch.zeros((130, 2 * d), device="cuda", dtype=torch.bfloat16)
+    P.attention(q, k, vt, o, q_prescaled=prescaled)
+    assert bool(o.isnan().all())
