@@ -622,6 +622,13 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const bf16* 
   }
   m_nx = m_run;
   int it = 0;
+  // The full-size d = 128 loop's time depends on where its code lies in the
+  // 32-byte fetch windows: 12 heads of 32760 tokens take 5247-5254 us with the
+  // loop's first instruction 20, 28, 0 or 4 bytes into one, 5267-5277 at 8, 12,
+  // 16 or 24 (16 placements, nine runs each).  Pinned to the start of one: the
+  // 15 words from here to the loop end at a 64-byte boundary.  The other
+  // forms showed no such difference.
+  if constexpr (D == 128 && KS == 1 && kPre) asm volatile(".p2align 6\n\ts_nop 0");
   for (; it + 1 < nkv; it += 2) {
     iter(sa, sb, it);
     iter(sb, sa, it + 1);

@@ -138,3 +138,28 @@ def test_hot_kernels_keep_memory_in_flight(kernels):
     if checked == 0:
         pytest.skip("llvm-objdump not found")
     assert checked >= 30
+
+
+def test_full_size_attention_loop_is_aligned(tmp_path):
+    """The main loop of the full-size d = 128 attention kernel starts at a
+    64-byte boundary: half of the other placements cost 0.5% of its time."""
+    obj = os.path.join(BUILD, "attention.o")
+    if not os.path.exists(obj) or not _tool("llvm-objdump"):
+        pytest.skip("no build objects or no llvm-objdump")
+    assert _kernels_of(obj, str(tmp_path))
+    dis = subprocess.run([_tool("llvm-objdump"), "-d", "--no-show-raw-insn",
+                          os.path.join(str(tmp_path), "attention.o.co")], check=True,
+                         capture_output=True, text=True).stdout
+    name, base, loops = None, 0, []
+    for line in dis.splitlines():
+        m = re.match(r"^([0-9a-f]+) <(\S+)>:", line)
+        if m:
+            base, name = int(m.group(1), 16), m.group(2)
+        elif name and "attn_bf16_kernelILi128ELi8ELb1ELi1E" in name:
+            m = re.search(r"s_c?branch\S* (\d+)\s+// ([0-9A-F]+):", line)
+            if m:
+                off, at = int(m.group(1)), int(m.group(2), 16)
+                off -= 65536 if off >= 32768 else 0
+                loops.append((-4 * off, at + 4 + 4 * off - base))  # bytes back, target
+    length, target = max(loops)
+    assert length > 2048 and base % 64 == 0 and target % 64 == 0, (length, target)
