@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_form.h"
 
 namespace acid {
 
@@ -195,11 +196,10 @@ __device__ __forceinline__ void tile_coords(uint32_t t, int64_t tiles_m, int til
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BM = kGemmTile, BN = kGemmTile, BK = kGemmStep;
 constexpr int kWaves = 8;                // 2 (tokens) x 4 (features), two per SIMD
 constexpr int kTileElems = 256 * BK;     // one operand tile per stage (32 KB)
 constexpr int64_t kSplitItemFloats = 256 * 256;  // one K-split partial tile (256 KB)
-constexpr int64_t kSplitMaxItems = 256;           // work items the split workspace holds
 
 // One 16-byte-per-lane LDS-DMA: lane l reads 16 bytes at base + off(l) and
 // writes LDS bytes [lds + 16 l, +16).  base and lds are wave-uniform.
@@ -1038,81 +1038,6 @@ __global__ __launch_bounds__(512, OCC) void gemm_f32_kernel(const float* A, cons
   }
 }
 
-// K split of the last round's tiles: when the tiles beyond whole rounds of
-// the device's CUs would leave at least half of them idle, those `rem` tiles
-// are split into S K ranges (S <= 8, S * rem within the CUs and the 256 work
-// items the workspace holds, each range a multiple of 128).  Each range is at
-// least 2048 long: a work item also fills the staging ring and writes its
-// 256 KB of partial sums, which the reduction reads back, and with shorter
-// ranges that costs more than the fuller round saves (measured: split into
-// K ranges of 256-1024, the small configuration's GEMMs ran twice as long).
-int choose_split(int64_t tiles, int K, int64_t& rem) {
-  const int cus = device_cus();
-  rem = tiles % cus;
-  if (rem == 0 || 2 * rem > cus) return 1;
-  int S = (int)(cus / rem);
-  if (S > 8) S = 8;
-  while (S > 1 && (rem * S > kSplitMaxItems || K % (S * 128) != 0 || K / S < 2048)) --S;
-  return S;
-}
-
-// Output tile and K split of a bf16 launch: the form with the least estimated
-// time, in microseconds: rounds of the CUs x (a + b x K-steps of 64), fitted
-// to the block's four products in place (weights not in the caches), 64 to
-// 6000 rows, N and K 256 to 12288 (15% rms of each time; the choices take
-// 1.4% more than the best of the forms at each size).
-// Microseconds, 256 x 256 / 256 x 128 / 128 x 128 / 64 x 64:
-//    256 x  3072 x  1024:  25.5 /  20.2 /  14.4 /   9.0
-//   1000 x  8960 x  1536:  41.2 /  51.2 /  58.7 /  60.6
-//   1560 x  1536 x  1536:  35.9 /  24.3 /  18.4 /  21.3
-//   1560 x  4608 x  1536:  36.2 /  30.3 /  36.6 /  44.3
-//   4000 x 12288 x  3072: 251.0 / 295.7 / 357.0 / 473.9
-// With a workspace the K range of a ring tile may be split too, where all
-// items fit one round: 64 rows x 1536 x 8960 45.1 -> 18.3 us, 300 rows 40.7
-// -> 26.4, 1000 rows 72.5 -> 43.7, 1560 rows 65.8 -> 59.0.  The second pass
-// costs about 6 us and its bytes at 4 TB/s.  Every tile without a split gives
-// the same bits.
-enum class Tile { k256, k256x128, k128, k64 };
-struct Form {
-  Tile tile;
-  int split;  // of a ring tile's K range, or of the 256 x 256 tail tiles'
-};
-Form choose_form(int64_t M, int N, int K, bool have_ws, int64_t& rem) {
-  const int64_t cus = device_cus(), tiles = (M + BM - 1) / BM * ((N + BN - 1) / BN);
-  const int steps = K / BK;
-  auto second_pass = [](int64_t items, int area) { return 6.0 + items * area * 1e-6; };
-  const int tail = have_ws ? choose_split(tiles, K, rem) : 1;
-  Form f = {Tile::k256, tail};
-  double best = (double)((tiles + cus - 1) / cus) * (17.5 + 0.84 * steps);
-  if (tail > 1)  // the last round takes a part of its K-steps
-    best += second_pass(rem * tail, BM * BN) - 0.84 * (steps - steps / tail);
-  auto consider = [&](Tile t, int tm, int tn, double once, double a, double b, double smooth) {
-    const int64_t n = (M + tm - 1) / tm * (N / tn);
-    const double x = (double)n / cus;
-    // smooth: part of a partly filled round that shares its CUs with the last
-    const double rounds = (1 - smooth) * (double)((n + cus - 1) / cus) + smooth * (x > 1 ? x : 1);
-    const double whole = once + rounds * (a + b * steps);
-    if (whole < best) {
-      best = whole;
-      f = {t, 1};
-    }
-    if (!have_ws) return;
-    for (int sp = 2; sp <= 8; ++sp) {
-      if (n * sp > cus || n * sp > kSplitMaxItems || steps / sp < 8) break;
-      const double cost =
-          once + a + b * ((steps + sp - 1) / sp) + second_pass(n * sp, tm * tn);
-      if (cost < best) {
-        best = cost;
-        f = {t, sp};
-      }
-    }
-  };
-  consider(Tile::k256x128, 256, 128, 0, 10, 0.75, 0);
-  consider(Tile::k128, 128, 128, 1, 6, 0.5, 0);
-  consider(Tile::k64, 64, 64, 4.7, 0.55, 0.225, 0.45);
-  return f;
-}
-
 // Grid of a ring kernel: one workgroup per tile, in two dimensions beyond 2^22
 // (a dimension holds fewer than 2^32 work-items).
 dim3 ring_grid(int64_t tiles) {
@@ -1146,9 +1071,9 @@ hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const 
                        const Epi& e, hipStream_t s) {
   if (dtype == ACID_BF16) {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    int64_t rem = 0;
-    const Form f = choose_form(M, N, K, e.split_ws != nullptr, rem);
+    const Form f = choose_form(M, N, K, e.split_ws != nullptr, device_cus());
     const int split = f.split;
+    const int64_t rem = f.rem;
     switch (f.tile) {
       case Tile::k256x128: return launch_ring<KIND, 256, 128, 4, 2, 3, 3>(M, N, K, a, wt, e, s, split);
       case Tile::k128: return launch_ring<KIND, 128, 128, 2, 4, 4, 3>(M, N, K, a, wt, e, s, split);

@@ -1,0 +1,70 @@
+"""The rule that chooses a bf16 GEMM's tile and K split (host code): what it
+takes at sizes measured on an MI355X, and the bounds its launches rely on."""
+import random
+
+import pytest
+
+from gemm_form_util import TILES, gemm_form
+
+DIMS = {"256x256": (256, 256), "256x128": (256, 128), "128x128": (128, 128), "64x64": (64, 64)}
+
+
+# rows, N, K and the measured microseconds of the four tiles in TILES' order
+@pytest.mark.parametrize("M,N,K,us", [
+    (256, 3072, 1024, (25.5, 20.2, 14.4, 9.0)),
+    (1000, 8960, 1536, (41.2, 51.2, 58.7, 60.6)),
+    (1560, 1536, 1536, (35.9, 24.3, 18.4, 21.3)),
+    (1560, 4608, 1536, (36.2, 30.3, 36.6, 44.3)),
+    (4000, 12288, 3072, (251.0, 295.7, 357.0, 473.9)),
+    (6000, 1536, 128, (12.2, 15.6, 15.3, 14.0)),
+    (8200, 1536, 128, (13.9, 16.4, 18.7, 18.1)),
+    (8200, 2176, 256, (25.5, 28.4, 27.9, 27.8)),
+    (17776, 640, 128, (13.3, 15.7, 15.4, 16.4)),
+    (24000, 640, 3072, (122.5, 85.1, 103.2, 142.5)),
+    (32760, 1536, 1536, (135.5, 156.6, 186.8, 247.5)),
+    (60000, 2176, 128, (118.3, 138.8, 161.6, 182.5)),
+    (60000, 8960, 128, (420.6, 487.2, 550.9, 684.9)),
+    (119056, 640, 256, (87.7, 102.5, 126.4, 145.8)),
+    (119056, 8960, 128, (824.0, 949.1, 1091.7, 1356.8)),
+])
+def test_fastest_measured_tile_is_taken(M, N, K, us):
+    tile, split, _ = gemm_form(M, N, K)
+    assert split == 1
+    assert us[TILES.index(tile)] <= 1.02 * min(us), (tile, us)
+
+
+def test_splits_stay_within_the_workspace():
+    """Every split: its items within one round of the CUs and the 256 the
+    workspace holds, K ranges of at least 8 K-steps (ring tiles) or 2048
+    (tail tiles of the 256 x 256 kernel, multiples of 128); none without a
+    workspace."""
+    rng = random.Random(5)
+    seen = set()
+    for _ in range(20000):
+        M = int(2 ** rng.uniform(0, 17))
+        N, K = 128 * rng.randint(1, 96), 128 * rng.randint(1, 160)
+        cus = rng.choice((256, 256, 304, 64))
+        assert gemm_form(M, N, K, False, cus)[1] == 1
+        tile, split, rem = gemm_form(M, N, K, True, cus)
+        tm, tn = DIMS[tile]
+        n = -(-M // tm) * -(-N // tn)
+        seen.add((tile, split > 1))
+        if split == 1:
+            continue
+        if tile == "256x256":
+            assert rem == n % cus and 0 < 2 * rem <= cus and K % (128 * split) == 0 and K // split >= 2048
+        else:
+            assert rem == 0 and K // 64 // split >= 8
+            rem = n
+        assert 2 <= split <= 8 and rem * split <= min(cus, 256)
+    assert seen == {(t, s) for t in TILES for s in (False, True)}
+
+
+def test_launches_of_many_rounds_take_the_largest_tile():
+    """From four rounds of 256 x 256 tiles on, the largest tile measured best
+    everywhere but at K = 256, where 256 x 128 is within 8% of it."""
+    rng = random.Random(6)
+    for _ in range(3000):
+        N, K = 256 * rng.randint(1, 48), 128 * rng.randint(3, 32)
+        M = (4 * 256 // (N // 256) + rng.randint(1, 400)) * 256
+        assert gemm_form(M, N, K)[0] == "256x256", (M, N, K)
