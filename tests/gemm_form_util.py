@@ -37,3 +37,8 @@ def gemm_form(M, N, K, workspace=False, cus=256):
     out = (C.c_int64 * 3)()
     _lib().form(C.c_int64(M), N, K, int(workspace), C.c_int64(cus), out)
     return TILES[out[0]], int(out[1]), int(out[2])
+
+
+def device_cus():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count

@@ -10,20 +10,22 @@ import pytest
 import torch
 
 import oracle as O
+from gemm_form_util import device_cus, gemm_form
 from gpu_util import assert_elementwise, need_gpu, to_np
 
 pytestmark = pytest.mark.gpu
 
-HEADS, D = 8, 64
+D = 64
 
 
 def _run(P, kind, a, wt, bias, gate, base, rows):
     a = a[:rows].contiguous()
     M, N = rows, wt.shape[0]
     if kind == "qkv":
-        q, k = (torch.empty((HEADS, M, D), dtype=torch.bfloat16, device="cuda") for _ in range(2))
-        vt = torch.zeros((HEADS, D, (M + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda")
-        P.linear(a, wt, P.ACID_EPI_QKV, bias, q=q, k=k, vt=vt, n_heads=HEADS, head_dim=D,
+        nh = N // (3 * D)
+        q, k = (torch.empty((nh, M, D), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        vt = torch.zeros((nh, D, (M + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda")
+        P.linear(a, wt, P.ACID_EPI_QKV, bias, q=q, k=k, vt=vt, n_heads=nh, head_dim=D,
                  q_prescale=True)
         # token-major [M][3 H], as the plain product
         return torch.cat([q.permute(1, 0, 2).reshape(M, -1), k.permute(1, 0, 2).reshape(M, -1),
@@ -45,17 +47,22 @@ def _run(P, kind, a, wt, bias, gate, base, rows):
 
 @pytest.mark.parametrize("kind", ["bias", "gelu", "gate_residual", "euler", "qkv"])
 @pytest.mark.parametrize("N,K,full,rows", [
-    # 256 x 256 for the full call; 64 x 64 up to 1031 rows, 128 x 128 at 1559
-    # and 1600, 256 x 128 at 4671 and 4864; K of two and of six stages (fewer
-    # than, and more than, the staging rings hold)
-    (1536, 128, 9000, (1, 63, 64, 65, 1031, 1559, 1600, 4671, 4864)),
-    (1536, 384, 9000, (33, 257, 1559, 4671)),
+    # 256 x 256 for the full call and the rows below for each smaller tile; K of
+    # two and of six stages (fewer than, and more than, the staging rings hold)
+    (1536, 128, 9000, {"64x64": (1, 63, 64, 65, 1031), "128x128": (1559, 1600),
+                       "256x128": (4671, 4864)}),
+    (1536, 384, 9000, {"64x64": (33, 257), "128x128": (1559,), "256x128": (4671,)}),
     # a half-width last feature tile of the 256 x 256 kernel
-    (2176, 128, 60000, (31, 1031))])
+    (2176, 128, 60000, {"64x64": (31,), "128x128": (1031,)}),
+    (2176, 384, 4100, {"64x64": (31,), "128x128": (1031,), "256x128": (2500,)}),
+    (1152, 384, 7600, {"64x64": (257,), "128x128": (1801,), "256x128": (3601,)})])
 def test_prefix_rows_same_bits_whatever_the_tile(kind, N, K, full, rows):
-    if kind == "qkv" and N != 3 * HEADS * D:
-        pytest.skip("the QKV split fixes N")
+    if kind == "qkv" and N % (3 * D):
+        pytest.skip("no head count gives this N")
     P = need_gpu()
+    assert gemm_form(full, N, K, False, device_cus())[0] == "256x256"
+    for tile, ms in rows.items():
+        assert [gemm_form(m, N, K, False, device_cus())[0] for m in ms] == [tile] * len(ms)
     g = torch.Generator(device="cuda")
     g.manual_seed(N + K)
     a = torch.randn((full, K), generator=g, device="cuda").bfloat16()
@@ -73,10 +80,10 @@ def test_prefix_rows_same_bits_whatever_the_tile(kind, N, K, full, rows):
     ref, tol = {"bias": (y, acc), "gelu": (O.gelu_tanh(y), 1.13 * acc + 1e-6),
                 "gate_residual": (b + to_np(gate) * y, np.abs(to_np(gate)) * acc + 2.0 ** -22 * (np.abs(b) + np.abs(y * to_np(gate)))),
                 "euler": (b - 0.25 * y, 0.25 * acc + 2.0 ** -22 * (np.abs(b) + np.abs(y))),
-                "qkv": (y * np.where(np.arange(N) < HEADS * D, P.q_scale(D), 1.0), acc)}[kind]
+                "qkv": (y * np.where(np.arange(N) < N // 3, P.q_scale(D), 1.0), acc)}[kind]
     rtol = 1.01 * 2.0 ** -8 if kind in ("gelu", "qkv") else 2.0 ** -22
     assert_elementwise(to_np(whole[at]), ref, tol, rtol, f"{kind} {full} x {N} x {K}")
-    for m in rows:
+    for m in sum(rows.values(), ()):
         got = _run(P, kind, a, wt, bias, gate, base, m)
         assert torch.equal(got, whole[:m]), (kind, m)
 
@@ -88,6 +95,7 @@ def test_k_split_step_repeats_bits():
     import acid_inputs as ai
     P = need_gpu()
     cfg = ai.COG5B.replace(n_blocks=1, n_steps=1)
+    assert gemm_form(cfg.n_tokens, cfg.hidden, cfg.ffn, True, device_cus()) == ("256x256", 3, 72)
     m = P.Model(cfg, max_steps=1)
     g = torch.Generator(device="cuda")
     g.manual_seed(4)

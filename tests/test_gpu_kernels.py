@@ -13,6 +13,7 @@ import torch
 
 import acid_inputs as ai
 import oracle as O
+from gemm_form_util import device_cus, gemm_form
 from gpu_util import (BF16_U, assert_elementwise, attention_bound, bf16_values, make_model,
                       need_gpu, rel_err, to_dev, to_np)
 
@@ -275,6 +276,7 @@ def test_linear_large_tiles_ragged(P, kind):
     N = 2176, a half-width last feature tile."""
     M, K = 8200, 256
     N = 2304 if kind.startswith("qkv") else 2176
+    assert gemm_form(M, N, K, False, device_cus())[0] == "256x256"
     # the qkv case in _linear_case uses d = 64: 2304 = 3 x 12 x 64
     for got, ref, tol, atol in _linear_case(P, kind, M, N, K, torch.bfloat16, seed=17):
         assert rel_err(got, ref) < tol, kind

@@ -14,6 +14,7 @@ import torch
 
 import acid_inputs as ai
 import oracle as O
+from gemm_form_util import device_cus, gemm_form
 from gpu_util import assert_close_to_scale, make_model, need_gpu, rel_err, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
@@ -23,8 +24,8 @@ SMALL_BF16 = ai.DiTConfig("small-bf16-ragged", n_blocks=2, hidden=256, n_heads=2
                           ffn=640, n_video=300, n_text=7, dtype="bf16", n_steps=8)
 SMALL_BF16_D64 = SMALL_BF16.replace(name="small-bf16-d64", n_heads=4, head_dim=64, n_text=0,
                                     n_video=257)
-# FFN 4096 over 2 row tiles: the second FFN GEMM (K = 4096) splits its tiles
-# into two K ranges with a fixed-order reduction of the partial sums
+# FFN 4096 over 307 rows: the second FFN GEMM (K = 4096) takes 64 x 64 tiles in
+# eight K ranges with a fixed-order reduction of the partial sums
 SMALL_BF16_SPLIT = SMALL_BF16.replace(name="small-bf16-ksplit", ffn=4096)
 
 
@@ -71,6 +72,7 @@ def test_dit_step_bf16_k_split_is_deterministic(P):
     """The K-split GEMM's reduction adds the partial sums in a fixed order:
     repeated steps are bit-identical."""
     cfg = SMALL_BF16_SPLIT
+    assert gemm_form(cfg.n_tokens, cfg.hidden, cfg.ffn, True, device_cus()) == ("64x64", 8, 0)
     m, _ = make_model(P, cfg, max_steps=4, std=0.05)
     xd = to_dev(ai.latents(cfg))
     td = to_dev(ai.text_tokens(cfg))
