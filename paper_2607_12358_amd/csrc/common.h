@@ -133,11 +133,13 @@ hipError_t launch_sinusoid(const float* sigmas_host, int n, int freq_dim, float*
                            hipStream_t s);
 // Y[s][n] = act_out( X[s][:] . W[:, n] + b[n] ) (act_out: 0 none, 1 SiLU), batched over `batch`
 // groups with element strides for W, b and the output column offset; W's
-// rows are ldw elements apart, N is a multiple of 128.
+// rows are ldw elements apart, N is a multiple of 128.  of_columns: where
+// these are some of a larger product's columns, the number of its columns
+// (all groups); the sums are then the ones that product forms, bit for bit.
 hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float* W, int ldw,
                               int N, const float* b, float* Y, int64_t ldy, int act_out,
                               int batch, int64_t w_stride, int64_t b_stride, int64_t y_stride,
-                              hipStream_t s);
+                              hipStream_t s, int64_t of_columns = 0);
 
 // GEMMs (gemm.hip)
 // split_ws: for bf16, a workspace of kGemmSplitWsBytes with which grids whose

@@ -389,14 +389,16 @@ acid_status modulation_table(acid_model* m, const float* sigmas, int n, float* t
 // Block 0's (shift1, scale1) at one noise level, the pair that TEMNI uses:
 // the first 2 H of the 6 H columns of its adaLN weights, of which a whole
 // row of the table reads n_blocks x 6 H (1.7 GB at the Wan-1.3B shape, 0.35
-// ms of a 0.48 ms drift signal, against 19 MB).
+// ms of a 0.48 ms drift signal, against 19 MB).  The same bits as the table's,
+// so that a caller's own loop sees the signals of acid_denoise_loop.
 acid_status temni_pair(acid_model* m, float sigma, float* pair, hipStream_t s) {
   const int H = m->cfg.hidden;
   return run(m, ACID_K_TEMB, s, "timestep modulation", [&]() {
     hipError_t err = timestep_conditioning(m, &sigma, 1, s);
     if (err == hipSuccess)
       err = launch_skinny_gemm(m->kp(m->kl.temb_u), H, 1, H, m->bp(0, m->wl.ada_w), 6 * H, 2 * H,
-                               m->bp(0, m->wl.ada_b), pair, 2 * H, 0, 1, 0, 0, 0, s);
+                               m->bp(0, m->wl.ada_b), pair, 2 * H, 0, 1, 0, 0, 0, s,
+                               (int64_t)m->cfg.n_blocks * 6 * H);
     return err;
   });
 }

@@ -36,9 +36,10 @@ __global__ void sinusoid_kernel(SigmaPack sig, int n, int freq_dim, float* __res
 // w + NW, ...): lane (half-wave h, index l) loads X[l][8 g + 4 h ..+3] and
 // W[8 g + 4 h + i][n0 + CB l ..+CB-1], so MFMA i of a group contracts
 // k = 8 g + i and 8 g + 4 + i, and one load of W is the operand of CB column
-// blocks.  Two or three groups are kept in flight per wave.  The waves' partial sums
-// meet in LDS and are added in wave order (deterministic, and independent of
-// RB: a row's values do not depend on how many rows the call holds).
+// blocks.  Two, three or eight groups are kept in flight per wave.  The waves'
+// partial sums meet in LDS and are added in wave order (deterministic, and
+// independent of RB and CB: a row's values depend neither on how many rows the
+// call holds nor on how many columns a workgroup has).
 // 50 rows x 30 x (1536 x 9216): the 16-rows-at-a-time VALU kernel took 1277
 // us, this one 545 (MFMAs on rows padded to 64: 346; one row: 316 us, 5.4
 // TB/s); the table with its three small products 1793 -> 594 us.  Two column
@@ -49,7 +50,7 @@ __global__ __launch_bounds__(64 * NW, CB == 4 ? 2 : 4) void skinny_gemm_kernel(
     const float* __restrict__ bias, float* __restrict__ Y, int64_t ldy, int act_out,
     int64_t w_stride, int64_t b_stride, int64_t y_stride) {
   typedef float wvec __attribute__((ext_vector_type(CB)));
-  constexpr int D = CB == 4 ? 2 : 3;  // groups in flight
+  constexpr int D = CB == 4 ? 2 : NW == 16 ? 3 : 8;  // groups in flight
   __shared__ wvec lds[NW * 16 * 64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -174,7 +175,7 @@ hipError_t launch_sinusoid(const float* sigmas_host, int n, int freq_dim, float*
 hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float* W, int ldw,
                               int N, const float* b, float* Y, int64_t ldy, int act_out,
                               int batch, int64_t w_stride, int64_t b_stride, int64_t y_stride,
-                              hipStream_t s) {
+                              hipStream_t s, int64_t of_columns) {
   if (S == 0 || batch == 0) return hipSuccess;
   if (N % 128 != 0 || ((uintptr_t)W % 16) != 0 || (w_stride % 4) != 0 || (ldw % 4) != 0 ||
       ((uintptr_t)b % 16) != 0 || (b_stride % 4) != 0)
@@ -188,10 +189,16 @@ hipError_t launch_skinny_gemm(const float* X, int ldx, int S, int K, const float
   // 128 columns and a four-way K split per workgroup where that gives the
   // CUs a workgroup each (then 64 rows share a read of W); otherwise 32
   // columns, 32 rows and a sixteen-way split: a 1536 x 1536 product of 50
-  // rows is 12 workgroups of the one and 96 of the other.  The choice does
-  // not look at S, so that a row's sums do not either.
-  if ((int64_t)(N / 128) * batch < 256)
+  // rows is 12 workgroups of the one and 96 of the other.  The split does
+  // not look at S, so that a row's sums do not either, and where a call forms
+  // some columns of a larger product (of_columns) it is that product's, so that
+  // both give the same bits: 32 columns, four waves (the pair of a drift
+  // signal at the Wan-1.3B shape, 1536 x 3072 of 1536 x 276480).
+  const int64_t own = (int64_t)N * batch, of = of_columns > own ? of_columns : own;
+  if (of / 128 < device_cus())
     SKINNY(1, 1, 16);
+  else if (own / 128 < device_cus())
+    SKINNY(1, 1, 4);
   else if (S <= 32)
     SKINNY(1, 4, 4);
   else

@@ -91,3 +91,30 @@ def test_loop_signals_of_nan_latents(mode):
             if mode != "easycache":  # its first signal needs two computed steps
                 assert bool(tr["s"][1] != tr["s"][1]) == bad
         assert got[0] == got[1] == got[2]
+
+
+@pytest.mark.parametrize("blocks,heads", [(1, 4), (11, 8)])
+def test_callers_own_loop_sees_the_same_signals(blocks, heads):
+    """acid_drift_signal forms one pair of the modulation table, a loop all of
+    it; TEMNI and signal are the same bits (11 blocks of hidden 512: the table
+    is wide enough for another K split than the pair by itself would take)."""
+    P = need_gpu()
+    cfg = ai.TINY.replace(n_blocks=blocks, hidden=64 * heads, n_heads=heads, n_steps=4, n_video=40)
+    m = P.Model(cfg, max_steps=4)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(blocks)
+    for tid, (_, shape) in enumerate(ai.manifest(cfg)):
+        m.load_tensor(tid, torch.randn(shape, generator=g, device="cuda") * 0.05)
+    x0 = torch.randn((cfg.n_video, cfg.hidden), generator=g, device="cuda")
+    sig = ai.sigmas(4)
+    kw = dict(mode="acid", tau_low=0.05, tau_high=0.2, delta=0.01)
+    x = x0.clone()
+    want = m.denoise_loop(x, sig, **kw)["s"].copy()
+    prev, cur = torch.empty_like(x0), torch.empty_like(x0)
+    for i in range(4):
+        x = x0.clone()
+        if i:
+            m.denoise_loop(x, sig[: i + 1], **kw)  # x_i
+        s = m.drift_signal(x, float(sig[i]), prev if i else None, cur)
+        assert s == want[i] or (i == 0 and s != s), (i, s, want[i])
+        prev, cur = cur, prev
