@@ -390,7 +390,8 @@ acid_status acid_ln_modulate(int32_t out_dtype, const float* x_dev,
  * (the softmax then needs no per-score scaling); other values:
  * ACID_ERR_INVALID_ARG.  Size limits (ACID_ERR_SHAPE beyond them):
  * seq_len * n_heads < 2^26, and for bf16 head_dim * vt_ld * 2 < 2^31
- * (32-bit per-head offsets). */
+ * (32-bit per-head offsets) and ceil(seq_len / (2 d)) * n_heads < 2^30 / d
+ * (work-items of a launch). */
 acid_status acid_attention(int32_t dtype, int32_t n_heads, int64_t seq_len,
                            int32_t head_dim, const void* q_dev,
                            const void* k_dev, const void* vt_dev,

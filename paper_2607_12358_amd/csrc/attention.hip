@@ -737,8 +737,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
   // [wave][chunk][query] after it.
   __shared__ f32x4 lds[4 * NC * BT];
   __shared__ float ml[2][4][BT];
-  const uint32_t n_qt = (uint32_t)((L + BT - 1) / BT);
-  const uint32_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
+  const uint32_t n_qt = (uint32_t)((L + BT - 1) / BT), items = n_qt * n_heads;
+  const uint32_t bid = blockIdx.y * gridDim.x + blockIdx.x;
+  if (bid >= items) return;
+  const uint32_t item = attn_xcd_remap(bid, items);
   const int head = (int)(item / n_qt);
   const int64_t q0 = (int64_t)(item - head * n_qt) * BT;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -937,7 +939,10 @@ template <int D>
 hipError_t launch_f32(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
                       int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s, const int32_t* pred,
                       bool q_prescaled) {
-  dim3 grid((unsigned)((L + 31) / 32 * n_heads));
+  // Up to 2^26 workgroups (one query each of many heads), in two dimensions
+  // beyond 2^22: a dimension holds fewer than 2^32 work-items.
+  const int64_t items = (L + 31) / 32 * n_heads, gy = (items + (1 << 22) - 1) >> 22;
+  dim3 grid((unsigned)((items + gy - 1) / gy), (unsigned)gy);
   hipLaunchKernelGGL(attn_f32_kernel<D>, grid, dim3(256), 0, s, (const float*)q,
                      (const float*)k, (const float*)vt, L, vt_ld, n_heads, (float*)o, o_ld,
                      q_prescaled ? 1.0f : attn_q_scale(D), pred);

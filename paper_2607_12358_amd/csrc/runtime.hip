@@ -89,7 +89,10 @@ acid_status check_attention_size(int dtype, int n_heads, int64_t L, int d, int64
   const int64_t lim = 0x7fffffff;
   if (dtype == ACID_BF16 && vt_ld > lim / (2 * d))
     return set_error(ACID_ERR_SHAPE, "bf16 attention: head_dim * vt_ld * 2 bytes must be < 2^31");
-  if (L > lim / 32 || L * n_heads > lim / 32)  // the fp32 kernel: 64 work-items per query
+  // bf16: a workgroup of 512 work-items per 256 queries (d = 128), or of 256 per 128
+  const int64_t bq = 2 * (int64_t)d, wg = 4 * (int64_t)d;
+  if (L > lim / 32 || L * n_heads > lim / 32 ||
+      (dtype == ACID_BF16 && (L + bq - 1) / bq * n_heads >= ((int64_t)1 << 32) / wg))
     return set_error(ACID_ERR_SHAPE, "attention: seq_len %lld x n_heads %d exceeds the grid limit",
                      (long long)L, n_heads);
   return ACID_OK;

@@ -93,6 +93,15 @@ def test_kernel_size_limits_checked(lib):
     assert attn(L.ACID_BF16, 1, 9_000_000, 64) == L.ACID_ERR_INVALID_ARG  # within: NULL check
     assert attn(L.ACID_F32, 64, 2_000_000, 64) == L.ACID_ERR_SHAPE     # L n_heads >= 2^26
     assert attn(L.ACID_F32, 32, 2_000_000, 64) == L.ACID_ERR_INVALID_ARG
+    # the launch's work-items: 2^32 / 512 workgroups of 256 queries at d = 128,
+    # 2^32 / 256 of 128 at d = 64; the fp32 grid folds, up to the limit above
+    for d in (64, 128):
+        most = (1 << 30) // d
+        assert attn(L.ACID_BF16, most, 1, d) == L.ACID_ERR_SHAPE
+        assert attn(L.ACID_BF16, most - 1, 1, d) == L.ACID_ERR_INVALID_ARG
+        assert attn(L.ACID_BF16, most // 2, 2 * d + 1, d) == L.ACID_ERR_SHAPE
+        assert attn(L.ACID_F32, (1 << 26) - 1, 1, d) == L.ACID_ERR_INVALID_ARG
+        assert attn(L.ACID_F32, 1 << 26, 1, d) == L.ACID_ERR_SHAPE
     e = L.EpilogueArgsC()
     e.kind = L.ACID_EPI_BIAS
     for M, N, K, st in [(1 << 20, 1 << 23, 128, L.ACID_ERR_SHAPE), (8, 128, 1 << 23, L.ACID_ERR_SHAPE),

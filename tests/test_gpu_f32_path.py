@@ -59,6 +59,23 @@ def test_attention_f32_masked_keys_have_no_weight(d):
     np.testing.assert_allclose(to_np(o), ref, rtol=2e-5, atol=2e-5)
 
 
+def test_attention_f32_more_heads_than_a_grid_dimension_holds():
+    """One query of 2^24 + 3 heads: 2^32 work-items and more, in a folded grid."""
+    P = need_gpu()
+    nh, d = (1 << 24) + 3, 64
+    q, k = (torch.ones((nh, 1, d), device="cuda") for _ in range(2))
+    vt = torch.zeros((nh, d, 8), device="cuda")
+    v = torch.arange(nh, device="cuda", dtype=torch.float32)[:, None] + 1.0
+    vt[:, :, 0] = v
+    o = torch.empty((1, nh * d), device="cuda")
+    P.attention(q, k, vt, o)
+    del q, k, vt
+    # a weight of 1 after one rounding each of p, l and their quotient
+    assert float((o.view(nh, d) / v - 1.0).abs().max()) <= 2.0 ** -21
+    del o, v
+    torch.cuda.empty_cache()
+
+
 F32_KINDS = ["bias", "gelu", "gate_residual", "euler", "qkv"]
 
 
