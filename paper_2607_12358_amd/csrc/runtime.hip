@@ -633,7 +633,10 @@ acid_status drift(acid_model* m, const float* row, const float* x, const float* 
 // loop, whose host would otherwise wait for the stream's completion signal as
 // well (1024-token loop 2462 -> 2258 us, 128-token fp32 loop 371 -> 315).  Not
 // for calls that return with the stream synchronised, nor while an earlier
-// launch may still write the slot.
+// launch may still write the slot.  A wait that outlasts it is for a copy, as
+// without a slot: the runtime spins for that on the calling thread alone, for a
+// stream also on one of its own (eight full-size steps of 435 ms took 503 ms of
+// processor time, 435 with the copy, whose few microseconds do not count there).
 constexpr uint64_t kUnwritten = 0x7ff8a5a55a5a1234ull;
 bool signal_arm(acid_model* m, int n) {
   if (!m->hres || m->hres_pending) return false;
@@ -649,6 +652,8 @@ bool signal_poll(acid_model* m, int n) {
     else if (++spins % 64 == 0 &&
              std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(500))
       return false;
+    else
+      __builtin_ia32_pause();
   }
   m->hres_pending = false;
   return true;
@@ -667,13 +672,14 @@ acid_status l1_norms(acid_model* m, const float* a, const float* b, const float*
     m->hres_pending = true;
     return launch_l1_norms(a, b, c, n, part, max_groups, dres, s, nullptr, m->hres);
   }));
-  if (!(armed && signal_poll(m, 2))) {
-    if (!m->hres)
-      ACID_HIP(hipMemcpyAsync(out2, dres, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+  bool slot = armed && signal_poll(m, 2);
+  if (!slot) {
+    slot = m->hres && !armed;
+    if (!slot) ACID_HIP(hipMemcpyAsync(out2, dres, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     ACID_HIP(hipStreamSynchronize(s));
     m->hres_pending = false;
   }
-  if (m->hres) {
+  if (slot) {
     out2[0] = m->hres[0];
     out2[1] = m->hres[1];
   }
@@ -988,12 +994,13 @@ acid_status read_drift(acid_model* m, double* s_out, hipStream_t s, bool armed =
     *s_out = m->hres[0];
     return ACID_OK;
   }
-  if (!m->hres)
+  const bool slot = m->hres && !armed;
+  if (!slot)
     ACID_HIP(hipMemcpyAsync(s_out, m->kp<double>(m->kl.dres) + 2, sizeof *s_out,
                             hipMemcpyDeviceToHost, s));
   ACID_HIP(hipStreamSynchronize(s));
   m->hres_pending = false;
-  if (m->hres) *s_out = m->hres[0];
+  if (slot) *s_out = m->hres[0];
   return ACID_OK;
 }
 
