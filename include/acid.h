@@ -139,7 +139,8 @@ typedef struct {
 /* Kernel classes timed by the optional HIP-event timer. */
 typedef enum {
   ACID_K_TEMB = 0,     /* timestep embedding + modulation table */
-  ACID_K_LN_MOD = 1,   /* LayerNorm + adaLN modulate (GEMM operand) */
+  ACID_K_LN_MOD = 1,   /* LayerNorm + adaLN modulate (GEMM operand); the head's
+                          with the residual store / apply where there is one */
   ACID_K_GEMM_QKV = 2,
   ACID_K_ATTENTION = 3,
   ACID_K_GEMM_PROJ = 4,
@@ -147,7 +148,7 @@ typedef enum {
   ACID_K_GEMM_FFN2 = 6,
   ACID_K_GEMM_HEAD = 7, /* head GEMM (+ Euler update in the loop) */
   ACID_K_DRIFT = 8,     /* TEMNI + relative-L1 partial sums + final reduce */
-  ACID_K_CACHE = 9,     /* residual store / apply */
+  ACID_K_CACHE = 9,     /* EasyCache's offset store / reuse */
   ACID_K_MISC = 10,     /* residual-stream assembly, weight conversion */
   ACID_K_COUNT = 11
 } acid_kernel_class;

@@ -38,12 +38,6 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 __device__ __forceinline__ float gelu_tanh(float z) {
   // 0.5 z (1 + tanh(sqrt(2/pi) (z + 0.044715 z^3)))
   const float k0 = 0.7978845608028654f;

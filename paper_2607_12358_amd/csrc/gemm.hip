@@ -27,7 +27,7 @@
 //   Launches whose 256 x 256 tiles would leave CUs idle (few rows) take
 //   256 x 128, 128 x 128 or 64 x 64 tiles (gemm_ring_kernel), with the K range
 //   split too where it is long and the tiles few: one 1560-token 30-block step
-//   8.62 -> 5.82 ms, the 1024-token loop 5.47 -> 2.32 ms, a 226 x 3072 x 3072
+//   8.62 -> 5.82 ms, the 1024-token loop 5.47 -> 2.2 ms, a 226 x 3072 x 3072
 //   product 52.5 -> 11.4 us.
 // fp32 path: the fp32 matrix instruction on 64 x 64 or 32 x 32 tiles, for the
 //   fp32 configuration.
@@ -132,6 +132,7 @@ struct ColEpi {
     }
   }
   __device__ __forceinline__ void put(int64_t m, float acc) const {
+    static_assert(!kRmw, "read-modify-write kinds go through put_old");
     const float y = acc + bias;
     if constexpr (KIND == ACID_EPI_BIAS) {
       dst_f[m * stride] = y;
@@ -140,12 +141,9 @@ struct ColEpi {
         dst_t[m * stride] = (T)gelu_tanh_fast(y);
       else
         dst_t[m * stride] = (T)gelu_tanh(y);
-    } else if constexpr (KIND == ACID_EPI_GATE_RESIDUAL) {
-      float* h = dst_f + m * stride;
-      *h = *h + gate * y;
     } else if constexpr (KIND == ACID_EPI_QKV) {
       dst_t[m * stride] = (T)(y * qmul);
-    } else if constexpr (KIND == ACID_EPI_QKV_GELU) {
+    } else {
       float z = y * qmul;
       if (gelu) {
         if constexpr (sizeof(T) == 2)
@@ -154,10 +152,6 @@ struct ColEpi {
           z = gelu_tanh(y);
       }
       dst_t[m * stride] = (T)z;
-    } else {
-      if (v_f) v_f[m * stride] = y;
-      float* x = dst_f + m * stride;
-      *x = *x + dsigma * y;
     }
   }
 };
