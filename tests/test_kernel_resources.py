@@ -124,7 +124,20 @@ def test_matrix_kernels_fit_two_waves_per_simd(kernels):
 # stores begin) turns into one wait per element, and such a kernel shows
 # tens to hundreds of them; batched kernels wait a handful of times.
 WAIT_BUDGET = {"gemm_bf16_kernel": 10, "attn_bf16_kernel": 8, "ln_modulate_kernel": 3,
-               "temni_drift_kernel": 4, "cache_kernel": 4, "l1_partials_kernel": 3}
+               "temni_drift_kernel": 4, "cache_kernel": 4, "l1_partials_kernel": 3,
+               "gemm_ring_kernel": 10, "gemm_ring_reduce_kernel": 7, "attn_f32_kernel": 6,
+               "skinny_gemm_kernel": 6,
+               # ten of them in the register copy of operands off 16-byte alignment
+               "gemm_f32_kernel": 21}
+
+# Waves of a workgroup and workgroups per CU (four SIMDs of 512 registers, 160 KB
+# of LDS) that a kernel's split was chosen for.
+RESIDENT = {"gemm_ring_kernelILi%dELi64ELi64E": (8, 2), "gemm_ring_kernelILi%dELi128ELi128E": (12, 1),
+            "gemm_ring_kernelILi%dELi256ELi128E": (12, 1), "gemm_f32_kernelILi%dELi32E": (8, 2),
+            "gemm_f32_kernelILi%dELi64E": (8, 2), "gemm_ring_reduce_kernelILi%dE": (4, 4),
+            "attn_f32_kernelILi64E": (4, 2), "attn_f32_kernelILi128E": (4, 2),
+            "skinny_gemm_kernelILi1ELi1ELi16E": (16, 1), "skinny_gemm_kernelILi1ELi1ELi4E": (4, 4),
+            "skinny_gemm_kernelILi1ELi4ELi4E": (4, 2), "skinny_gemm_kernelILi2ELi4ELi4E": (4, 2)}
 
 
 def test_hot_kernels_keep_memory_in_flight(kernels):
@@ -138,6 +151,19 @@ def test_hot_kernels_keep_memory_in_flight(kernels):
     if checked == 0:
         pytest.skip("llvm-objdump not found")
     assert checked >= 30
+
+
+def test_kernels_fit_the_workgroups_they_were_split_for(kernels):
+    for key, (waves, groups) in RESIDENT.items():
+        for epi in range(6) if "%d" in key else (0,):
+            name = key % epi if "%d" in key else key
+            found = [k for ks in kernels.values() for k in ks if name in k["name"]]
+            assert found, name
+            for k in found:
+                regs = int(k["vgpr_count"]) + int(k.get("agpr_count", 0))
+                per_simd = -(-waves * groups // 4)
+                assert -(-regs // 8) * 8 * per_simd <= 512, (k["name"], regs)
+                assert int(k["group_segment_fixed_size"]) * groups <= 160 * 1024, k["name"]
 
 
 def test_full_size_attention_loop_is_aligned(tmp_path):
