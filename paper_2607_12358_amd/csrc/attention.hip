@@ -25,7 +25,8 @@
 //   arguments themselves.  The row sum adds the bf16-rounded probabilities
 //   that the P V product uses.
 // fp32 path: the fp32 matrix instruction, 32 queries per workgroup, the keys
-//   split over its four waves (for the fp32 configuration).
+//   split over its four waves (for the fp32 configuration); up to 18 tokens one
+//   wave per (head, query).
 #include <atomic>
 
 #include "common.h"
@@ -737,10 +738,8 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
   // [wave][chunk][query] after it.
   __shared__ f32x4 lds[4 * NC * BT];
   __shared__ float ml[2][4][BT];
-  const uint32_t n_qt = (uint32_t)((L + BT - 1) / BT), items = n_qt * n_heads;
-  const uint32_t bid = blockIdx.y * gridDim.x + blockIdx.x;
-  if (bid >= items) return;
-  const uint32_t item = attn_xcd_remap(bid, items);
+  const uint32_t n_qt = (uint32_t)((L + BT - 1) / BT);
+  const uint32_t item = attn_xcd_remap(blockIdx.x, n_qt * n_heads);
   const int head = (int)(item / n_qt);
   const int64_t q0 = (int64_t)(item - head * n_qt) * BT;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -883,6 +882,59 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
   }
 }
 
+// fp32 with few keys: one wave per (head, query), lane j takes key j's score
+// and the wave adds the values one key at a time, lane l for dims l, l + 64,
+// ....  Bound by its loads' latency.  The matrix kernel's chain for a single
+// tile of keys (64 or 128 MFMAs of 64 cycles, and the merge) takes longer there:
+// 24 heads of 64 / 128, 3 tokens 3.4 / 4.6 us against 5.8 / 9.3, 12 tokens 4.6 /
+// 6.9 against 5.4 / 8.5, 18 equal, 24 tokens 6.2 / 10.1 against 5.5 / 8.4.
+constexpr int kFewKeys = 18;  // at most 64
+template <int D>
+__global__ __launch_bounds__(256) void attn_f32_few_kernel(const float* __restrict__ Q,
+                                                           const float* __restrict__ Kp,
+                                                           const float* __restrict__ Vt, int64_t L,
+                                                           int64_t vt_ld, int n_heads,
+                                                           float* __restrict__ O, int64_t o_ld,
+                                                           float scale, const int32_t* pred) {
+  if (pred && *pred == 0) return;
+  constexpr int C = D / 64;  // output dims per lane
+  const int lane = threadIdx.x & 63, Li = (int)L;
+  const uint32_t wq = (blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (wq >= (uint32_t)Li * n_heads) return;  // whole wave; no barriers below
+  const int head = (int)(wq / (uint32_t)Li);
+  const int64_t qrow = wq - (uint32_t)head * Li;
+  const float* Vh = Vt + (int64_t)head * D * vt_ld;
+  float s = -__builtin_inff();
+  if (lane < Li) {
+    const float4* q4 = reinterpret_cast<const float4*>(Q + ((int64_t)head * L + qrow) * D);
+    const float4* k4 = reinterpret_cast<const float4*>(Kp + ((int64_t)head * L + lane) * D);
+    float a = 0.f;
+#pragma unroll
+    for (int d4 = 0; d4 < D / 4; ++d4) {
+      const float4 qv = q4[d4], kv = k4[d4];
+      a += qv.x * kv.x + qv.y * kv.y + qv.z * kv.z + qv.w * kv.w;
+    }
+    s = a * scale;
+  }
+  float m = s;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  const float p = lane < Li ? exp2f(s - m) : 0.f;
+  const float inv = 1.0f / wave_sum(p);
+  float o[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) o[c] = 0.f;
+#pragma unroll 4
+  for (int j = 0; j < Li; ++j) {
+    const float pj = __shfl(p, j, 64);
+#pragma unroll
+    for (int c = 0; c < C; ++c) o[c] += pj * Vh[(int64_t)(lane + 64 * c) * vt_ld + j];
+  }
+  float* orow = O + qrow * o_ld + (int64_t)head * D;
+#pragma unroll
+  for (int c = 0; c < C; ++c) orow[lane + 64 * c] = o[c] * inv;
+}
+
 template <int D, int NW, bool kPre, int KS>
 hipError_t launch_bf16_form(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
                             int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s,
@@ -939,13 +991,21 @@ template <int D>
 hipError_t launch_f32(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
                       int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s, const int32_t* pred,
                       bool q_prescaled) {
-  // Up to 2^26 workgroups (one query each of many heads), in two dimensions
-  // beyond 2^22: a dimension holds fewer than 2^32 work-items.
-  const int64_t items = (L + 31) / 32 * n_heads, gy = (items + (1 << 22) - 1) >> 22;
-  dim3 grid((unsigned)((items + gy - 1) / gy), (unsigned)gy);
+  const float scale = q_prescaled ? 1.0f : attn_q_scale(D);
+  if (L <= kFewKeys) {
+    // Up to 2^24 workgroups of four queries, in two dimensions beyond 2^22: a
+    // dimension holds fewer than 2^32 work-items.
+    const int64_t wgs = (L * n_heads + 3) / 4, gy = (wgs + (1 << 22) - 1) >> 22;
+    hipLaunchKernelGGL(attn_f32_few_kernel<D>, dim3((unsigned)((wgs + gy - 1) / gy), (unsigned)gy),
+                       dim3(256), 0, s, (const float*)q, (const float*)k, (const float*)vt, L,
+                       vt_ld, n_heads, (float*)o, o_ld, scale, pred);
+    return hipGetLastError();
+  }
+  // Fewer than 2^22 workgroups: seq_len * n_heads is below 2^26.
+  dim3 grid((unsigned)((L + 31) / 32 * n_heads));
   hipLaunchKernelGGL(attn_f32_kernel<D>, grid, dim3(256), 0, s, (const float*)q,
-                     (const float*)k, (const float*)vt, L, vt_ld, n_heads, (float*)o, o_ld,
-                     q_prescaled ? 1.0f : attn_q_scale(D), pred);
+                     (const float*)k, (const float*)vt, L, vt_ld, n_heads, (float*)o, o_ld, scale,
+                     pred);
   return hipGetLastError();
 }
 

@@ -59,8 +59,36 @@ def test_attention_f32_masked_keys_have_no_weight(d):
     np.testing.assert_allclose(to_np(o), ref, rtol=2e-5, atol=2e-5)
 
 
+@pytest.mark.parametrize("prescaled", [False, True], ids=["plain-q", "prescaled-q"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L", [1, 3, 17, 18, 19])
+def test_attention_f32_few_keys(L, d, prescaled):
+    """One wave per query up to 18 keys, the matrix kernel from 19 on; V^T's
+    padding is NaN, more queries than a workgroup's four, a masked key."""
+    P = need_gpu()
+    nh = 5
+    rng = np.random.default_rng(L + d)
+    q, k, v = (rng.normal(size=(nh, L, d)).astype(np.float32) for _ in range(3))
+    keep = np.ones(L, bool)
+    if L > 3:
+        q[:, :, 0] = 1.0
+        k[:, 2, 0] = -np.inf
+        keep[2] = False
+    q_dev = (q * np.float32(P.q_scale(d))).astype(np.float32) if prescaled else q
+    vt = np.full((nh, d, 24), np.nan, np.float32)
+    vt[:, :, :L] = v.transpose(0, 2, 1)
+    o = torch.empty((L, nh * d), device="cuda")
+    P.attention(to_dev(q_dev), to_dev(k), to_dev(vt), o, q_prescaled=prescaled)
+    for j in range(nh):
+        kj, vj = k[j][keep], v[j][keep]
+        assert_elementwise(to_np(o[:, j * d:(j + 1) * d]), O.attention(q[j], kj, vj),
+                           1.05 * attention_bound(q[j], kj, vj, False), 3e-5,
+                           f"fp32 few keys L={L} d={d} head {j}")
+
+
 def test_attention_f32_more_heads_than_a_grid_dimension_holds():
-    """One query of 2^24 + 3 heads: 2^32 work-items and more, in a folded grid."""
+    """One query of 2^24 + 3 heads: the few-keys kernel's workgroups fold into two
+    grid dimensions."""
     P = need_gpu()
     nh, d = (1 << 24) + 3, 64
     q, k = (torch.ones((nh, 1, d), device="cuda") for _ in range(2))
