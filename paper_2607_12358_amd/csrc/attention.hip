@@ -29,6 +29,7 @@
 //   wave per (head, query).
 #include <atomic>
 
+#include "attn_form.h"
 #include "common.h"
 
 namespace acid {
@@ -962,26 +963,18 @@ hipError_t launch_bf16_form(int n_heads, int64_t L, const void* q, const void* k
 }
 
 // Waves per workgroup: 8 for d = 128 (a staged K/V tile feeds 256 queries),
-// 4 for d = 64 (finer grid for the shorter sequences of that configuration).
-// Short sequences, whose workgroups would leave CUs idle, split the keys over
-// the waves instead: d = 64 in four (64 queries a workgroup) or two (128), d =
-// 128 in two (128), the most that gives at most one workgroup per CU.  In one
-// round it runs 1.3-1.8 times as fast (12 heads of 128: 1024 tokens 31.5 ->
-// 21.4 us, 1560 44.5 -> 30.3, 2340 60.8 -> 45.1; 16 heads of 64, 1024 tokens:
-// 20.6 -> 12.8); with two rounds it loses (3000 tokens 74.0 -> 98.1 us; 16
-// heads of 64, 4096 tokens 86.8 -> 124.9), since a split workgroup fills its
-// CU's LDS or registers alone and streams K and V for fewer queries.
+// 4 for d = 64 (finer grid for the shorter sequences of that configuration),
+// 8 where the keys are split.
 template <int D, bool kPre>
 hipError_t launch_bf16(int n_heads, int64_t L, const void* q, const void* k, const void* vt,
                        int64_t vt_ld, void* o, int64_t o_ld, hipStream_t s,
                        const int32_t* pred) {
-  const int64_t cus = device_cus();
-  auto one_round = [&](int queries) { return (L + queries - 1) / queries * n_heads <= cus; };
+  const int ranges = attn_key_ranges(D, n_heads, L, device_cus());
   if constexpr (D == 64) {
-    if (one_round(64))
+    if (ranges == 4)
       return launch_bf16_form<64, 8, kPre, 4>(n_heads, L, q, k, vt, vt_ld, o, o_ld, s, pred);
   }
-  if (one_round(128))
+  if (ranges == 2)
     return launch_bf16_form<D, 8, kPre, 2>(n_heads, L, q, k, vt, vt_ld, o, o_ld, s, pred);
   return launch_bf16_form<D, D == 128 ? 8 : 4, kPre, 1>(n_heads, L, q, k, vt, vt_ld, o, o_ld, s,
                                                         pred);

@@ -1,6 +1,7 @@
-"""The output tile and K split that a bf16 GEMM launch takes, from the
-library's own rule (csrc/gemm_form.h compiled for the host), so that a test
-can state which kernel its sizes reach."""
+"""The output tile and K split that a bf16 GEMM launch takes, and the key
+ranges of a bf16 attention launch, from the library's own rules
+(csrc/gemm_form.h, csrc/attn_form.h compiled for the host), so that a test can
+state which kernel its sizes reach."""
 import ctypes as C
 import functools
 import os
@@ -11,7 +12,11 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 TILES = ("256x256", "256x128", "128x128", "64x64")
 
 SRC = """
+#include "attn_form.h"
 #include "gemm_form.h"
+extern "C" int ranges(int d, int64_t n_heads, int64_t L, int64_t cus) {
+  return acid::attn_key_ranges(d, n_heads, L, cus);
+}
 extern "C" void form(int64_t M, int N, int K, int ws, int64_t cus, int64_t* out) {
   const acid::Form f = acid::choose_form(M, N, K, ws != 0, cus);
   out[0] = (int)f.tile;
@@ -37,6 +42,11 @@ def gemm_form(M, N, K, workspace=False, cus=256):
     out = (C.c_int64 * 3)()
     _lib().form(C.c_int64(M), N, K, int(workspace), C.c_int64(cus), out)
     return TILES[out[0]], int(out[1]), int(out[2])
+
+
+def attn_ranges(d, n_heads, L, cus=256):
+    """Key ranges that the waves of a workgroup take (1: not split)"""
+    return _lib().ranges(d, C.c_int64(n_heads), C.c_int64(L), C.c_int64(cus))
 
 
 def device_cus():

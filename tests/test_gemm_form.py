@@ -1,10 +1,11 @@
-"""The rule that chooses a bf16 GEMM's tile and K split (host code): what it
-takes at sizes measured on an MI355X, and the bounds its launches rely on."""
+"""The rules that choose a bf16 GEMM's tile and K split and a bf16 attention's
+key ranges (host code): what they take at sizes measured on an MI355X, and the
+bounds the launches rely on."""
 import random
 
 import pytest
 
-from gemm_form_util import TILES, gemm_form
+from gemm_form_util import TILES, attn_ranges, gemm_form
 
 DIMS = {"256x256": (256, 256), "256x128": (256, 128), "128x128": (128, 128), "64x64": (64, 64)}
 
@@ -68,3 +69,23 @@ def test_launches_of_many_rounds_take_the_largest_tile():
         N, K = 256 * rng.randint(1, 48), 128 * rng.randint(3, 32)
         M = (4 * 256 // (N // 256) + rng.randint(1, 400)) * 256
         assert gemm_form(M, N, K)[0] == "256x256", (M, N, K)
+
+
+# head dim, heads, tokens and the measured microseconds without and with a split
+@pytest.mark.parametrize("d,nh,L,whole,split", [
+    (64, 16, 17, 3.6, 4.8), (128, 16, 17, 5.3, 6.2), (64, 16, 64, 3.7, 5.0), (128, 16, 64, 5.8, 6.6),
+    (64, 48, 100, 5.7, 6.0), (64, 16, 129, 6.7, 5.9), (64, 16, 200, 8.4, 5.9), (128, 16, 200, 13.3, 10.9),
+    (64, 16, 1024, 20.6, 12.8), (128, 12, 1024, 31.5, 21.4), (128, 12, 2340, 60.8, 45.1),
+    (128, 12, 3000, 74.0, 98.1), (64, 16, 4096, 86.8, 124.9)])
+def test_keys_are_split_where_that_measured_faster(d, nh, L, whole, split):
+    assert (attn_ranges(d, nh, L) > 1) == (split < whole)
+
+
+def test_split_attention_takes_one_round():
+    rng = random.Random(7)
+    for _ in range(5000):
+        d, nh, L = rng.choice((64, 128)), rng.randint(1, 64), rng.randint(1, 40000)
+        r = attn_ranges(d, nh, L)
+        assert r in ((1, 2, 4) if d == 64 else (1, 2))
+        if r > 1:  # eight waves of 32 queries in r groups
+            assert L >= 128 and -(-L // (256 // r)) * nh <= 256

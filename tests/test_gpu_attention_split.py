@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import oracle as O
+from gemm_form_util import attn_ranges, device_cus
 from gpu_util import BF16_U, assert_elementwise, attention_bound, bf16_values, need_gpu, to_dev, to_np
 from test_gpu_kernels import prescale_q
 
@@ -37,10 +38,13 @@ def _case(P, nh, L, d, prescaled, std=1.0, check=(0,), grow=False):
 
 @pytest.mark.parametrize("prescaled", [False, True], ids=["plain-q", "prescaled-q"])
 @pytest.mark.parametrize("d", [64, 128])
-# 1 to 9 tiles of 64 keys, with and without a ragged one; 1037: 17 tiles
+# 1 to 9 tiles of 64 keys, with and without a ragged one (split from 128 on);
+# 1037: 17 tiles
 @pytest.mark.parametrize("nh", [2, 20])  # d = 64: four ranges, or two (from 833 tokens on)
 @pytest.mark.parametrize("L", [1, 33, 64, 65, 128, 129, 192, 255, 256, 257, 320, 383, 576, 1037, 1408])
 def test_split_over_key_ranges(L, nh, d, prescaled):
+    want = 1 if L < 128 else 2 if d == 128 or (nh == 20 and L >= 833) else 4
+    assert attn_ranges(d, nh, L, device_cus()) == want
     _case(need_gpu(), nh, L, d, prescaled, check=(0, 1))
 
 
@@ -54,6 +58,7 @@ def test_split_with_growing_scores(d, prescaled):
 @pytest.mark.parametrize("d,nh", [(64, 1024), (128, 600)])
 @pytest.mark.parametrize("L", [64, 130, 320])
 def test_unsplit_at_short_lengths(L, d, nh, prescaled):
+    assert attn_ranges(d, nh, L, device_cus()) == 1
     _case(need_gpu(), nh, L, d, prescaled, check=(0, nh // 2, nh - 1))
 
 
@@ -114,6 +119,7 @@ def test_masked_tile_is_no_reference(value, far, d, prescaled):
     range, a masked ragged tile (processed first), and the unsplit kernel."""
     P = need_gpu()
     L = 512
+    assert attn_ranges(d, 2, L, device_cus()) == 256 // d and attn_ranges(d, 300, 150, device_cus()) == 1
     for t in range(8):
         at = np.zeros(L, bool)
         at[64 * t:64 * t + 64] = True
