@@ -1065,7 +1065,11 @@ hipError_t launch_kind(int dtype, int64_t M, int N, int K, const void* a, const 
                        const Epi& e, hipStream_t s) {
   if (dtype == ACID_BF16) {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    const Form f = choose_form(M, N, K, e.split_ws != nullptr, device_cus());
+    constexpr Out kOut = KIND == ACID_EPI_BIAS        ? Out::kPlain
+                         : KIND == ACID_EPI_BIAS_GELU ? Out::kGelu
+                         : ColEpi<KIND, bf16>::kRmw   ? Out::kUpdate
+                                                      : Out::kHeads;
+    const Form f = choose_form(kOut, M, N, K, e.split_ws != nullptr, device_cus());
     const int split = f.split;
     const int64_t rem = f.rem;
     switch (f.tile) {

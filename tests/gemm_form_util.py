@@ -17,8 +17,8 @@ SRC = """
 extern "C" int ranges(int d, int64_t n_heads, int64_t L, int64_t cus) {
   return acid::attn_key_ranges(d, n_heads, L, cus);
 }
-extern "C" void form(int64_t M, int N, int K, int ws, int64_t cus, int64_t* out) {
-  const acid::Form f = acid::choose_form(M, N, K, ws != 0, cus);
+extern "C" void form(int epi, int64_t M, int N, int K, int ws, int64_t cus, int64_t* out) {
+  const acid::Form f = acid::choose_form((acid::Out)epi, M, N, K, ws != 0, cus);
   out[0] = (int)f.tile;
   out[1] = f.split;
   out[2] = f.rem;
@@ -37,10 +37,14 @@ def _lib():
     return C.CDLL(so)
 
 
-def gemm_form(M, N, K, workspace=False, cus=256):
+EPILOGUES = {"bias": 0, "gelu": 1, "gate_residual": 2, "euler": 2, "qkv": 3, "qkv_prescaled": 3,
+             "qkv_gelu": 3}
+
+
+def gemm_form(M, N, K, workspace=False, cus=256, kind="bias"):
     """(tile, K split, tail tiles that the split applies to; 0: all)"""
     out = (C.c_int64 * 3)()
-    _lib().form(C.c_int64(M), N, K, int(workspace), C.c_int64(cus), out)
+    _lib().form(EPILOGUES[kind], C.c_int64(M), N, K, int(workspace), C.c_int64(cus), out)
     return TILES[out[0]], int(out[1]), int(out[2])
 
 

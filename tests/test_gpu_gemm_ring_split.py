@@ -43,26 +43,28 @@ def _block(h, w, mod, heads, d, parallel):
 # 8 and 3 ranges (one row, a ragged row tile), 128 x 128 and 256 x 128 tiles (full
 # and ragged), ranges of unequal length (70 and 140 K-steps in 8, 3, 7 and 5),
 # the output projection and the GELU product at hidden 4096, the fused Q K V and
-# GELU product, and 256 x 256 tiles whose last round is split (Q K V, FFN2).
+# GELU product, and 256 x 256 tiles whose last round is split (Q K V, output).
 @pytest.mark.parametrize("rows,heads,d,ffn,form,tiles", [
     (1, 4, 64, 8192, "sequential", "64x64/1 64x64/1 64x64/1 64x64/8"),
     (65, 8, 64, 4480, "sequential", "64x64/1 64x64/1 64x64/1 64x64/8"),
     (130, 12, 128, 8960, "sequential", "64x64/1 64x64/1 64x64/1 64x64/3"),
     (300, 12, 128, 8960, "sequential", "64x64/1 64x64/1 128x128/1 128x128/7"),
-    (1000, 12, 128, 8960, "sequential", "256x128/1 64x64/1 256x256/1 256x128/5"),
+    (1000, 12, 128, 8960, "sequential", "64x64/1 64x64/1 256x256/1 256x128/5"),
     (1280, 12, 128, 8960, "parallel", "256x128/1 256x128/4"),
-    (70, 32, 128, 512, "sequential", "64x64/1 64x64/2 64x64/8 64x64/1"),
-    (128, 32, 128, 256, "sequential", "64x64/1 64x64/2 64x64/8 64x64/1"),
-    (65, 30, 128, 4096, "parallel", "128x128/2 128x128/8"),
+    (100, 32, 128, 512, "sequential", "128x128/2 64x64/2 64x64/8 64x64/1"),
+    (64, 32, 128, 256, "sequential", "64x64/1 64x64/4 64x64/8 64x64/1"),
+    (100, 30, 128, 4096, "parallel", "128x128/2 128x128/8"),
     (1500, 32, 128, 256, "sequential", "256x256/2 256x128/1 64x64/2 256x128/1"),
-    (1000, 24, 128, 12288, "sequential", "256x256/1 128x128/1 256x256/1 256x256/4"),
+    (4680, 32, 128, 256, "sequential", "256x256/1 256x256/2 128x128/3 256x256/1"),
 ])
 def test_block_with_split_products(rows, heads, d, ffn, form, tiles):
     P = need_gpu()
     H = heads * d
-    prods = [(3 * H, H), (H, H), (ffn, H), (H, ffn)] if form == "sequential" else \
-        [(3 * H + ffn, H), (H, H + ffn)]
-    assert " ".join("%s/%d" % gemm_form(rows, n, k, True, device_cus())[:2] for n, k in prods) == tiles
+    prods = [("qkv", 3 * H, H), ("gate_residual", H, H), ("gelu", ffn, H),
+             ("gate_residual", H, ffn)] if form == "sequential" else \
+        [("qkv_gelu", 3 * H + ffn, H), ("gate_residual", H, H + ffn)]
+    assert " ".join("%s/%d" % gemm_form(rows, n, k, True, device_cus(), kind)[:2]
+                    for kind, n, k in prods) == tiles
     cfg = ai.TINY.replace(dtype="bf16", n_blocks=1, hidden=H, n_heads=heads, head_dim=d, ffn=ffn,
                           n_video=rows, n_text=0, block=form)
     m = P.Model(cfg, max_steps=1)

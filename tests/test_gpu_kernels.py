@@ -274,9 +274,9 @@ def test_linear(P, kind, dtype, M, N, K):
 def test_linear_large_tiles_ragged(P, kind):
     """Large ragged shapes: ragged M over many 256-row tiles and, for
     N = 2176, a half-width last feature tile."""
-    M, K = 8200, 256
+    M, K = 7000, 256
     N = 2304 if kind.startswith("qkv") else 2176
-    assert gemm_form(M, N, K, False, device_cus())[0] == "256x256"
+    assert gemm_form(M, N, K, False, device_cus(), kind)[0] == "256x256"
     # the qkv case in _linear_case uses d = 64: 2304 = 3 x 12 x 64
     for got, ref, tol, atol in _linear_case(P, kind, M, N, K, torch.bfloat16, seed=17):
         assert rel_err(got, ref) < tol, kind

@@ -72,7 +72,8 @@ def test_dit_step_bf16_k_split_is_deterministic(P):
     """The K-split GEMM's reduction adds the partial sums in a fixed order:
     repeated steps are bit-identical."""
     cfg = SMALL_BF16_SPLIT
-    assert gemm_form(cfg.n_tokens, cfg.hidden, cfg.ffn, True, device_cus()) == ("64x64", 8, 0)
+    assert gemm_form(cfg.n_tokens, cfg.hidden, cfg.ffn, True, device_cus(),
+                     "gate_residual") == ("64x64", 8, 0)
     m, _ = make_model(P, cfg, max_steps=4, std=0.05)
     xd = to_dev(ai.latents(cfg))
     td = to_dev(ai.text_tokens(cfg))
